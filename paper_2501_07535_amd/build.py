@@ -30,6 +30,9 @@ FLAGS = [
     # butterflies partly rolled, and indexing the unit's element array inside a
     # rolled loop puts the array in scratch memory
     "-mllvm", "-pragma-unroll-threshold=100000000",
+    # keep a column's products in source order, carried word first: reassociated,
+    # they are summed from zero and the carry is added by an instruction of its own
+    "-mllvm", "-opt-disable=reassociate",
     "-Wall", "-Wno-unused-function",
 ]
 

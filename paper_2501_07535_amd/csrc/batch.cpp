@@ -117,11 +117,9 @@ static int batch_create(const moma_ntt_job_t* jobs, uint32_t njobs, BatchImpl& b
   // whether the modulus is full width (kernels of their own)
   typedef std::tuple<int, uint32_t, uint32_t, bool, size_t, bool, bool> GKey;
   std::map<GKey, Group> groups;
-  NttConsts none;
-  memset(&none, 0, sizeof(none));
   // one transform of a job: its passes go to phases phase0, phase0 + 1, ...
   auto add = [&](NttPlan& p, const NttSchedule& sched, const std::vector<NttPass>& passes, const DirTables& t,
-                 const NttConsts& nc, bool scale, const uint32_t* in, const uint32_t* in2, uint32_t* first_out,
+                 const uint32_t* scale, const uint32_t* in, const uint32_t* in2, uint32_t* first_out,
                  uint32_t* out, uint32_t phase0) {
     const FieldRaw& f = p.fe->f;
     size_t cb = ntt_consts_bytes(f.L, f.fw != 0);
@@ -139,7 +137,7 @@ static int batch_create(const moma_ntt_job_t* jobs, uint32_t njobs, BatchImpl& b
       a.k = ps.k;
       a.logc = ps.logc;
       a.last = (i + 1 == passes.size()) ? 1u : 0u;
-      a.scale = (scale && i + 1 == passes.size()) ? 1u : 0u;
+      a.scale = i + 1 == passes.size() ? scale : nullptr;
       const bool variant = !f.fw && ntt_batch_variant(f.L, sched.radix_log, sched.threads, &a);
       Group& g = groups[GKey(f.L, sched.radix_log, sched.threads, i == 0 && in2 != nullptr, tile_bytes, variant,
                              f.fw != 0)];
@@ -147,7 +145,7 @@ static int batch_create(const moma_ntt_job_t* jobs, uint32_t njobs, BatchImpl& b
       g.recs.push_back(a);
       size_t off = g.consts.size();
       g.consts.resize(off + cb);
-      ntt_fill_consts(f, p.fe->dc, &nc, g.consts.data() + off);
+      ntt_fill_consts(f, p.fe->dc, g.consts.data() + off);
       uint64_t E = 1ull << (ps.k + ps.logc);
       uint64_t cost = E * ps.k;
       uint32_t ph = phase0 + (uint32_t)i;
@@ -269,9 +267,9 @@ static int batch_create(const moma_ntt_job_t* jobs, uint32_t njobs, BatchImpl& b
       int r = alloc(2 * plane_words, &sa);
       if (r) return r;
       uint32_t* sb = sa + plane_words;
-      add(*p, sched, passes, p->fwd, none, false, job.d_in, nullptr, sa, sa, ph0);
-      add(*p, sched, passes, p->fwd, none, false, job.d_in2, nullptr, sb, sb, ph0);
-      add(*p, sched, passes, p->inv, p->mul_consts, true, sa, sb, job.d_out, job.d_out,
+      add(*p, sched, passes, p->fwd, nullptr, job.d_in, nullptr, sa, sa, ph0);
+      add(*p, sched, passes, p->fwd, nullptr, job.d_in2, nullptr, sb, sb, ph0);
+      add(*p, sched, passes, p->inv, p->mul_scale(), sa, sb, job.d_out, job.d_out,
           ph0 + (uint32_t)passes.size());
       if (f.Ls > f.L) b.fills.push_back({job.d_out, p->n, f.L, f.Ls});
       continue;
@@ -282,7 +280,7 @@ static int batch_create(const moma_ntt_job_t* jobs, uint32_t njobs, BatchImpl& b
       int r = alloc(plane_words, &first_out);
       if (r) return r;
     }
-    add(*p, sched, passes, inverse ? p->inv : p->fwd, inverse ? p->inv_consts : none, inverse, job.d_in, nullptr,
+    add(*p, sched, passes, inverse ? p->inv : p->fwd, inverse ? p->inv_scale() : nullptr, job.d_in, nullptr,
         first_out, job.d_out, ph0);
     if (f.Ls > f.L && job.d_out != job.d_in) b.fills.push_back({job.d_out, p->n, f.L, f.Ls});
   }

@@ -98,6 +98,7 @@ int build_field(const uint32_t* q, uint32_t limbs, std::shared_ptr<FieldEntry>* 
     memset(&dc, 0, sizeof(dc));
     int b = digit_bits(f.L), D = digit_count(f.L, f.fw);
     digits_of(Q, f.L, f.fw, dc.qd);
+    digits_of(HBig::sub(HBig::pow2(b * D), Q), f.L, f.fw, dc.nqd);
     dc.qinvd = f.qinv & ((1u << b) - 1);
     fe->adj = HBig::mod(HBig::pow2(b * D), Q);
     fe->adj.to_limbs(dc.adj, kMaxLimbs);
@@ -283,7 +284,7 @@ static int build_tables(NttPlan& p, const HBig& w, DirTables* t) {
   for (int j = 0; j < L; j++) lad[(size_t)(p.logn + 1) * L + j] = p.fe->dc.adj[j];
   int e = upload(&t->ladder, lad);
   if (e) return hip_fail(e, "ladder upload");
-  e = (int)hipMalloc((void**)&t->tw, (size_t)p.n * digit_stride(L, f.fw) * sizeof(uint32_t));
+  e = (int)hipMalloc((void**)&t->tw, (size_t)p.n * tw_words(L, f.fw) * sizeof(uint32_t));
   if (e) {
     t->tw = nullptr;
     free_tables(t);
@@ -364,15 +365,21 @@ int get_plan(const uint32_t* q, const uint32_t* omega, uint64_t n, uint32_t limb
   if (check_planes(*p)) return set_error(MOMA_E_UNSUPPORTED, "no valid pass split for this size");
   HBig Winv = HBig::powmod(W, HBig(n - 1), Q);
   HBig ninv = HBig::sub(Q, nq);  // n * (q - (q-1)/n) == 1 mod q
-  // last-pass scales in digit Montgomery form (R = 2^(bD)): n^-1 R for the
-  // inverse; n^-1 R^2 after the fused pointwise product of a cyclic product,
-  // which leaves a factor R^-1
-  const HBig& rd = fe->adj;
-  HBig nscale = HBig::mulmod(ninv, rd, Q);
-  memset(&p->inv_consts, 0, sizeof(p->inv_consts));
-  digits_of(nscale, fe->f.L, fe->f.fw, p->inv_consts.nscale_d);
-  memset(&p->mul_consts, 0, sizeof(p->mul_consts));
-  digits_of(HBig::mulmod(nscale, rd, Q), fe->f.L, fe->f.fw, p->mul_consts.nscale_d);
+  // last-pass scales: n^-1 for the inverse; n^-1 R (R = 2^(bD)) after the
+  // fused pointwise product of a cyclic product, which leaves a factor R^-1
+  const int bD = digit_bits(fe->f.L) * digit_count(fe->f.L, fe->f.fw);
+  const int D = digit_count(fe->f.L, fe->f.fw);
+  std::vector<uint32_t> sc((size_t)4 * D);
+  auto scale_digits = [&](const HBig& v, uint32_t* out) {
+    HBig vq;
+    HBig::divmod(HBig::shl(v, bD), Q, &vq, nullptr);
+    digits_of(vq, fe->f.L, fe->f.fw, out);
+    digits_of(v, fe->f.L, fe->f.fw, out + D);
+  };
+  scale_digits(ninv, sc.data());
+  scale_digits(HBig::mulmod(ninv, fe->adj, Q), sc.data() + 2 * D);
+  int e = upload(&p->scales, sc);
+  if (e) return hip_fail(e, "scale upload");
   rc = build_tables(*p, W, &p->fwd);
   if (rc) return rc;
   rc = build_tables(*p, Winv, &p->inv);
@@ -380,7 +387,7 @@ int get_plan(const uint32_t* q, const uint32_t* omega, uint64_t n, uint32_t limb
     free_tables(&p->fwd);  // (the plan's destructor would too; freed here so the failure path holds nothing)
     return rc;
   }
-  int e = (int)hipDeviceSynchronize();
+  e = (int)hipDeviceSynchronize();
   if (e) return hip_fail(e, "plan build");
   std::lock_guard<std::mutex> lk(g_mu);
   auto it = g_plans.find(key);
@@ -395,11 +402,11 @@ int get_plan(const uint32_t* q, const uint32_t* omega, uint64_t n, uint32_t limb
 
 // Enqueue the passes of one transform over the compute limbs.  d_in2, when
 // set, is multiplied into d_in element by element as the first pass loads
-// (a Montgomery product, so c must carry the matching scale).  first_out is
+// (a Montgomery product, so `scale` must be the matching one).  first_out is
 // where the first pass writes when there are several (the later ones work in
 // place on d_out).
 static int enqueue_passes(NttPlan& p, const std::vector<NttPass>& passes, const NttSchedule& sched,
-                          const DirTables& t, const NttConsts& c, bool scale, const uint32_t* d_in,
+                          const DirTables& t, const uint32_t* scale, const uint32_t* d_in,
                           const uint32_t* d_in2, uint32_t* first_out, uint32_t* d_out, hipStream_t s) {
   const FieldRaw& f = p.fe->f;
   size_t P = passes.size();
@@ -416,8 +423,8 @@ static int enqueue_passes(NttPlan& p, const std::vector<NttPass>& passes, const 
     a.k = ps.k;
     a.logc = ps.logc;
     a.last = (i + 1 == P) ? 1u : 0u;
-    a.scale = (scale && i + 1 == P) ? 1u : 0u;
-    int e = launch_ntt_pass(f, p.fe->dc, a, c, sched.threads, ps.tiles, sched.radix_log, sched.kara, s);
+    a.scale = i + 1 == P ? scale : nullptr;
+    int e = launch_ntt_pass(f, p.fe->dc, a, sched.threads, ps.tiles, sched.radix_log, sched.kara, s);
     if (e) return hip_fail(e, "ntt pass launch");
   }
   return MOMA_OK;
@@ -457,11 +464,8 @@ int run_plan(NttPlan& p, bool inverse, const uint32_t* d_in, uint32_t* d_out, hi
       first_out = p.scratch;
     }
   }
-  NttConsts none;
-  memset(&none, 0, sizeof(none));
   const DirTables& t = inverse ? p.inv : p.fwd;
-  const NttConsts& nc = inverse ? p.inv_consts : none;
-  int rc = enqueue_passes(p, passes, sched, t, nc, inverse, d_in, nullptr, first_out, d_out, s);
+  int rc = enqueue_passes(p, passes, sched, t, inverse ? p.inv_scale() : nullptr, d_in, nullptr, first_out, d_out, s);
   if (rc) return rc;
   if (f.Ls > f.L && d_out != d_in) {
     int e = launch_zero_planes(d_out, p.n, f.L, f.Ls, s);
@@ -494,11 +498,9 @@ int run_cyclic_mul(NttPlan& p, const uint32_t* d_a, const uint32_t* d_b, uint32_
   }
   uint32_t* sa = spec;
   uint32_t* sb = spec + (size_t)p.n * f.L;
-  NttConsts none;
-  memset(&none, 0, sizeof(none));
-  int rc = enqueue_passes(p, passes, sched, p.fwd, none, false, d_a, nullptr, sa, sa, s);
-  if (!rc) rc = enqueue_passes(p, passes, sched, p.fwd, none, false, d_b, nullptr, sb, sb, s);
-  if (!rc) rc = enqueue_passes(p, passes, sched, p.inv, p.mul_consts, true, sa, sb, d_out, d_out, s);
+  int rc = enqueue_passes(p, passes, sched, p.fwd, nullptr, d_a, nullptr, sa, sa, s);
+  if (!rc) rc = enqueue_passes(p, passes, sched, p.fwd, nullptr, d_b, nullptr, sb, sb, s);
+  if (!rc) rc = enqueue_passes(p, passes, sched, p.inv, p.mul_scale(), sa, sb, d_out, d_out, s);
   if (rc) return rc;
   if (f.Ls > f.L) {
     int e = launch_zero_planes(d_out, p.n, f.L, f.Ls, s);

@@ -8,18 +8,21 @@
 namespace moma {
 
 constexpr int kMaxLimbs = 32;
-// Digit form of the transform's twiddle multiply: b-bit digits (b = 29, or 28
-// above 28 limbs), D of them, so that 2D products of two digits plus a carry
-// stay below 2^64 and b*D >= 32L - 2 covers every operand below 4q.
+// Digit form of the transform's multiplies: b-bit digits (b = 29, or 28 above
+// 28 limbs), D of them, so that 2D products of two digits plus a carry stay
+// below 2^64, and b*D >= 32L - 1, so that an operand y below 4q <= 2^(32L-2)
+// is at most half of R = 2^(bD), as the fixed-operand product needs (only 20
+// limbs need a digit more for that than for covering 4q).
 // A full-width modulus (fw: bitlen(q) > 32L - 4) keeps canonical operands
-// below q < 2^(32L), so its digits cover 32L bits.
+// below q < 2^(32L); its digits cover 32L bits, and b never divides 32L, so
+// again y < R / 2.
 constexpr int digit_bits(int L) { return L <= 28 ? 29 : 28; }
 constexpr int digit_count(int L, bool fw = false) {
-  return (32 * L - (fw ? 0 : 2) + digit_bits(L) - 1) / digit_bits(L);
+  return (32 * L - (fw ? 0 : 1) + digit_bits(L) - 1) / digit_bits(L);
 }
-constexpr int digit_stride(int L, bool fw = false) {  // table words per entry
-  return digit_count(L, fw) + (digit_count(L, fw) & 1);
-}
+// words of one twiddle table entry: the quotient's digits, the twiddle's
+// digits, padded to whole 16-byte loads
+constexpr int tw_words(int L, bool fw = false) { return (2 * digit_count(L, fw) + 3) / 4 * 4; }
 
 // widest limb counts that get radix-4 / radix-8 / radix-16 register units
 // (radix 4 up to 16 limbs: 4 elements of 16 limbs plus the digit multiply fit
@@ -71,11 +74,12 @@ struct NttPassArgs {
   const uint32_t* in;
   const uint32_t* in2;  // first inverse pass of a cyclic product: multiply by in2 pointwise while loading, else NULL
   uint32_t* out;
-  const uint32_t* tw;  // twiddle table, element-major, digit_stride(L) words per entry
+  const uint32_t* scale;  // last pass of the inverse: the factor every element takes on store, else NULL (2 D digits:
+                          // its quotient's, then its own, as a twiddle's)
+  const uint32_t* tw;  // twiddle table, element-major, tw_words(L) words per entry
   uint64_t n;
   uint32_t logn, K, k, logc;
   uint32_t last;       // last pass: store canonical residues in [0, q)
-  uint32_t scale;      // multiply by n^-1 on store (last pass of the inverse)
   uint32_t direct;     // set by the pass launcher: the first round reads straight from `in`
 };
 
@@ -93,15 +97,10 @@ struct NttSchedule {
 enum NttArith { kArithLazy = 0, kArithFull = 1, kArithKara = 2 };
 
 
-struct NttConsts {
-  // last-pass scale of the inverse transform, as D b-bit digits: n^{-1} 2^(bD)
-  // mod q (times another 2^(bD) after a fused pointwise product)
-  uint32_t nscale_d[40];
-};
-
-// per-modulus constants of the digit-form multiply
+// per-modulus constants of the digit-form multiplies
 struct DigitConsts {
   uint32_t qd[40];   // q in b-bit digits (digit_count(L, fw) of them)
+  uint32_t nqd[40];  // 2^(bD) - q in digits
   uint32_t qinvd;    // -q^{-1} mod 2^b
   uint32_t adj[kMaxLimbs];  // 2^(b*D) mod q, converts a table entry to digit Montgomery form
 };
@@ -112,13 +111,13 @@ int set_error(int code, const std::string& detail);
 // launchers (return hipError_t as int)
 int launch_blas(int op, const FieldRaw& f, const BlasArgs& a, hipStream_t s);
 int launch_zero_planes(uint32_t* out, uint64_t n, int from_plane, int to_plane, hipStream_t s);
-int launch_ntt_pass(const FieldRaw& f, const DigitConsts& dc, const NttPassArgs& a, const NttConsts& c,
+int launch_ntt_pass(const FieldRaw& f, const DigitConsts& dc, const NttPassArgs& a,
                     uint32_t threads, uint64_t tiles, uint32_t radix_log, uint32_t kara, hipStream_t s);
 // batched transforms: one launch runs items (pass record, tile) of many plans
 // (fw: full-width moduli, whose kernels and constants are of their own kind)
 size_t ntt_consts_bytes(int L, bool fw);
 void ntt_batch_prepare(int L, uint32_t radix_log, bool fw, size_t lds);
-void ntt_fill_consts(const FieldRaw& f, const DigitConsts& dc, const NttConsts* nc, void* dst);
+void ntt_fill_consts(const FieldRaw& f, const DigitConsts& dc, void* dst);
 int launch_ntt_batch(int L, uint32_t radix_log, bool mul, bool variant, bool fw, uint32_t threads, size_t lds,
                      uint32_t grid, const NttPassArgs* d_passes, const void* d_consts, const uint2* d_items,
                      uint32_t nitems, hipStream_t s);

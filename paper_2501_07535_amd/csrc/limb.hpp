@@ -49,6 +49,27 @@ __device__ __forceinline__ T* load_global_ptr(T* const* slot) {
   return (T*)*static_cast<const GlobalPtr*>(static_cast<const void*>(slot));
 }
 
+// A pointer from a uniform base (an SGPR pair, kept apart from the lane's part:
+// the compiler would otherwise add the two per lane, in 64 bits) and a byte
+// offset of the lane: one global access with both.
+template <class T>
+__device__ __forceinline__ const T& uniform_at(const void* base, u32 lane_bytes) {
+  u64 b = (u64)base;
+  asm volatile("" : "+s"(b));
+  typedef const __attribute__((address_space(1))) char* GlobalBytes;
+  typedef const __attribute__((address_space(1))) T* GlobalT;
+  return *(const T*)(GlobalT)((GlobalBytes)b + lane_bytes);
+}
+
+template <class T>
+__device__ __forceinline__ void uniform_put(void* base, u32 lane_bytes, const T& v) {
+  u64 b = (u64)base;
+  asm volatile("" : "+s"(b));
+  typedef __attribute__((address_space(1))) char* GlobalBytes;
+  typedef __attribute__((address_space(1))) T* GlobalT;
+  *(T*)(GlobalT)((GlobalBytes)b + lane_bytes) = v;
+}
+
 // ----------------------------------------------------------------- word ops
 
 // acc(64) += x * y; hi += carry-out.  x in a VGPR, y in a VGPR.
@@ -267,20 +288,6 @@ __device__ __forceinline__ void to_digits(u32* d, const u32* y) {
   }
 }
 
-// y = the value of digits d, as L 32-bit limbs (the value fits 32L bits)
-template <int L, bool FW = false>
-__device__ __forceinline__ void from_digits(u32* y, const u32* d) {
-  constexpr int b = Digits<L, FW>::b, D = Digits<L, FW>::D;
-#pragma unroll
-  for (int j = 0; j < L; j++) {
-    const int pos = 32 * j, i = pos / b, s = pos % b;
-    u32 v = d[i] >> s;
-    if (i + 1 < D && b - s < 32) v |= d[i + 1] << (b - s);
-    if (i + 2 < D && 2 * b - s < 32) v |= d[i + 2] << (2 * b - s);
-    y[j] = v;
-  }
-}
-
 // t = y * w * 2^(-bD) mod q in [0, 2q), w given as digits (Montgomery form for
 // R = 2^(bD)), y < 4q in 32-bit limbs (y < q for a full-width modulus, FW).
 // Product scanning: column i sums every digit product y_j w_{i-j} and
@@ -337,78 +344,148 @@ __device__ __forceinline__ void mont_mul_digits(u32* t, const u32* y, const u32*
   if constexpr (FW) *top = (u32)bits;  // bit 32L of a full-width result below 2q
 }
 
-// The same product with its first half (the digit product y w) by one level
-// of Karatsuba (Eq. (mulk)) on the digits: with y = y1 B^h + y0 and
-// w = w1 B^h + w0 (B = 2^b, h = ceil(D/2)), y w = z2 B^(2h) + z1 B^h + z0 where
+// Fixed-operand product (Shoup's method as in Harvey, "Faster arithmetic for
+// number-theoretic transforms", J. Symb. Comp. 2014, carried to digits): the
+// table holds the twiddle w < q and its scaled quotient wq = floor(w R / q),
+// R = 2^(bD).  With m = floor(wq y / R),
+//   t = w y - m q   lies in [0, 2q) and needs only its low D digits.
+// So one product is taken from its top columns, two from their low ones: about
+// 3/2 D^2 digit products, and no reduction multiply per column, against 2 D^2
+// plus D multiplies for the Montgomery product scan.
+//   * Quotient: columns D-2 .. 2D-2 of wq y.  The columns left out weigh less
+//     than (D-2) 2^-b R together, so m is floor(w y / q) or one less whenever
+//     y / R + (D-2) 2^-b < 1 (y < 4q: digit_count keeps y <= R/2).
+//   * t = low digits of (w y + m nq), nq = R - q: sums only.  A column holds
+//     2D digit products plus the carried word, as in the product scan.
+//   * t leaves as 32-bit limbs, two instructions per digit: a digit is shifted
+//     to the top of its word and one alignbit joins it with the next.
+// What bounds it is the issue of v_mad_u64_u32 (about 5 cycles of a SIMD each,
+// against 2.5 to 4.5 for the other integer instructions).  With the tile layout
+// in LDS and the uniform addressing that came with it, against the Montgomery
+// product scan: 245 instead of 306 VALU instructions per 256-bit butterfly;
+// 2^20 points 126.3 -> 119.4 us at 256 bits, 1248 -> 1013 us at 1024 bits; 2^14
+// points at 384 bits 39.0 -> 31.4 us.
+// (Summing two columns side by side, for independent chains where a SIMD has
+// only one wave, was no faster: 256 bits, 2^12 points 20.8 -> 21.1 us.)
+template <int L, bool FW = false>
+__device__ __forceinline__ void quot_digits(u32* m, const u32* a, const u32* wq) {
+  constexpr int b = Digits<L, FW>::b, D = Digits<L, FW>::D;
+  u64 acc = 0;
+#pragma unroll
+  for (int c = D - 2; c <= 2 * D - 2; c++) {
+#pragma unroll
+    for (int j = (c < D ? 0 : c - D + 1); j <= (c < D ? c : D - 1); j++) acc += (u64)a[j] * wq[c - j];
+    if (c >= D) m[c - D] = (u32)acc & Digits<L, FW>::mask;
+    acc >>= b;
+  }
+  m[D - 1] = (u32)acc;
+}
+
+// limbs of a value given as raw columns: raw[i]'s low b bits are digit i (the
+// bits above are ignored, except in the last digit)
+template <int L, bool FW = false>
+__device__ __forceinline__ void raw_to_limbs(u32* t, const u32* raw, u32* top) {
+  constexpr int b = Digits<L, FW>::b, D = Digits<L, FW>::D;
+  u32 hi[D];  // the digit at the top of its word
+#pragma unroll
+  for (int i = 0; i < D - 1; i++) hi[i] = raw[i] << (32 - b);
+#pragma unroll
+  for (int j = 0; j <= L; j++) {
+    if (j == L && !FW) break;
+    const int pos = 32 * j, i = pos / b, s = pos % b;  // the limb's lowest bit: bit s of digit i
+    u32 v;
+    if (i >= D) {
+      v = 0;
+    } else if (i == D - 1) {
+      v = raw[i] >> s;
+    } else {
+      // digit i from bit s up, then digit i + 1 (all of it where b - s + b < 32)
+      const int have = 2 * b - s;
+      v = __builtin_amdgcn_alignbit(raw[i + 1], hi[i], 32 - b + s);
+      if (have < 32 && i + 1 < D - 1) {
+        v = (hi[i] >> (32 - b + s)) | ((raw[i + 1] << (32 - b)) >> (32 - b) << (b - s));
+        if (i + 2 < D) v |= raw[i + 2] << have;
+      }
+    }
+    if (j < L)
+      t[j] = v;
+    else
+      *top = v;
+  }
+}
+
+template <int L, bool FW = false>
+__device__ __forceinline__ void quot_mul(u32* t, const u32* y, const u32* w, const u32* wq, const u32* nqd,
+                                         u32* top = nullptr) {
+  constexpr int b = Digits<L, FW>::b, D = Digits<L, FW>::D;
+  u32 a[D], m[D], raw[D];
+  to_digits<L, FW>(a, y);
+  quot_digits<L, FW>(m, a, wq);
+  u64 acc = 0;
+#pragma unroll
+  for (int i = 0; i < D; i++) {
+#pragma unroll
+    for (int j = 0; j <= i; j++) {
+      acc += (u64)a[j] * w[i - j];
+      acc += (u64)m[j] * nqd[i - j];
+    }
+    // the last column's high word is not needed, but left to see that the
+    // compiler takes a mul_lo and half an add3 in place of each v_mad_u64_u32
+    if (i == D - 1) asm("" : "+v"(acc));
+    raw[i] = (u32)acc;
+    acc >>= b;
+  }
+  raw[D - 1] &= Digits<L, FW>::mask;  // t < 2q <= R: what is above is the discarded multiple of R
+  raw_to_limbs<L, FW>(t, raw, top);
+}
+
+// The same product with w y by one level of Karatsuba (Eq. (mulk)) on the
+// digits, of which the low D columns are needed: with y = y1 B^h + y0 and
+// w = w1 B^h + w0 (B = 2^b, h = ceil(D/2)), w y = z0 + z1 B^h + ... where
 // z1 = (y0 + y1)(w0 + w1) - z0 - z2.  The digit sums have b + 1 bits and need
 // no carry; every product column is gathered as an exact 64-bit sum (it
-// equals the schoolbook column, below D 2^(2b)), so the Montgomery
-// reduction that follows is unchanged.  Word products: 2h^2 + (D - h)^2
-// instead of D^2, for 2D - 1 extra column additions and 2h - 1 column
-// subtractions.
+// equals the schoolbook column).
 template <int L>
-__device__ __forceinline__ void mont_mul_digits_kara(u32* t, const u32* y, const u32* wd, const u32* qd, u32 qinvd) {
+__device__ __forceinline__ void quot_mul_kara(u32* t, const u32* y, const u32* w, const u32* wq, const u32* nqd) {
   constexpr int b = Digits<L>::b, D = Digits<L>::D, h = (D + 1) / 2, g = D - h;
-  constexpr u32 mask = Digits<L>::mask;
-  u32 a[D], m[D], r[D], sa[h], sw[h];
+  u32 a[D], m[D], raw[D], sa[h], sw[h];
   to_digits<L>(a, y);
+  quot_digits<L>(m, a, wq);
 #pragma unroll
   for (int i = 0; i < h; i++) {
     sa[i] = a[i] + (i < g ? a[h + i] : 0u);
-    sw[i] = wd[i] + (i < g ? wd[h + i] : 0u);
+    sw[i] = w[i] + (i < g ? w[h + i] : 0u);
   }
-  u64 p[2 * D - 1];
+  u64 p[D];
 #pragma unroll
-  for (int c = 0; c < 2 * D - 1; c++) p[c] = 0;
+  for (int c = 0; c < D; c++) p[c] = 0;
 #pragma unroll
-  for (int c = 0; c < 2 * h - 1; c++) {
-    u64 z0 = 0, zm = 0, z2 = 0;
+  for (int c = 0; c < (2 * h - 1 < D ? 2 * h - 1 : D); c++) {
+    u64 z0 = 0;
 #pragma unroll
-    for (int i = (c < h ? 0 : c - h + 1); i <= (c < h ? c : h - 1); i++) {
-      z0 += (u64)a[i] * wd[c - i];
-      zm += (u64)sa[i] * sw[c - i];
-    }
-    if (c <= 2 * g - 2) {
-#pragma unroll
-      for (int i = (c < g ? 0 : c - g + 1); i <= (c < g ? c : g - 1); i++) z2 += (u64)a[h + i] * wd[h + c - i];
-      p[c + 2 * h] += z2;
-    }
+    for (int i = (c < h ? 0 : c - h + 1); i <= (c < h ? c : h - 1); i++) z0 += (u64)a[i] * w[c - i];
     p[c] += z0;
-    p[c + h] += zm - z0 - z2;  // the cross terms: exact, non-negative
+    if (c + h < D) {
+      u64 zm = 0, z2 = 0;
+#pragma unroll
+      for (int i = 0; i <= c; i++) {
+        zm += (u64)sa[i] * sw[c - i];
+        if (i < g && c - i < g) z2 += (u64)a[h + i] * w[h + c - i];
+      }
+      p[c + h] += zm - z0 - z2;  // the cross terms: exact, non-negative
+    }
   }
   u64 acc = 0;
 #pragma unroll
   for (int i = 0; i < D; i++) {
     acc += p[i];
 #pragma unroll
-    for (int j = 0; j < i; j++) acc += (u64)m[j] * qd[i - j];
-    m[i] = ((u32)acc * qinvd) & mask;
-    acc += (u64)m[i] * qd[0];
+    for (int j = 0; j <= i; j++) acc += (u64)m[j] * nqd[i - j];
+    raw[i] = (u32)acc;
     acc >>= b;
   }
-#pragma unroll
-  for (int i = D; i < 2 * D - 1; i++) {
-    acc += p[i];
-#pragma unroll
-    for (int j = i - D + 1; j < D; j++) acc += (u64)m[j] * qd[i - j];
-    r[i - D] = (u32)acc & mask;
-    acc >>= b;
-  }
-  r[D - 1] = (u32)acc;
-  from_digits<L>(t, r);
-}
-
-// Lazy butterfly with the Karatsuba form of the twiddle multiply.
-template <int L>
-__device__ __forceinline__ void ct_butterfly_kara(u32* x, u32* y, const u32* wd, const u32* qd, u32 qinvd,
-                                                  const u32* q2v) {
-  u32 xr[L], t[L], d[L], s[L];
-  u64 br = sub_vv<L>(s, x, q2v);  // x - 2q; borrow <=> x < 2q
-  select<L>(xr, br, x, s);
-  mont_mul_digits_kara<L>(t, y, wd, qd, qinvd);
-  add_vv<L>(x, xr, t);
-  sub_vv<L>(d, xr, t);
-  add_vv<L>(y, d, q2v);
+  raw[D - 1] &= Digits<L>::mask;
+  raw_to_limbs<L>(t, raw, nullptr);
 }
 
 // ----------------------------------------------------------------- full width
@@ -451,10 +528,10 @@ __device__ __forceinline__ void mod_sub_v(u32* r, const u32* a, const u32* b, co
 // Canonical butterfly for a full-width modulus: x, y in [0, q), twiddle in
 // digit form; x' = (x + wy) mod q, y' = (x - wy) mod q.
 template <int L>
-__device__ __forceinline__ void ct_butterfly_fw(u32* x, u32* y, const u32* wd, const u32* qd, u32 qinvd,
+__device__ __forceinline__ void ct_butterfly_fw(u32* x, u32* y, const u32* w, const u32* wq, const u32* nqd,
                                                 const u32* qv) {
   u32 t[L], tr[L], top;
-  mont_mul_digits<L, true>(t, y, wd, qd, qinvd, &top);
+  quot_mul<L, true>(t, y, w, wq, nqd, &top);
   reduce_top<L>(tr, t, top, qv);
   u32 s[L], d[L];
 #pragma unroll
@@ -526,22 +603,6 @@ __device__ __forceinline__ void to_vgprs(u32* dst, const u32* src) {
   for (int i = 0; i < L; i++) asm volatile("v_mov_b32 %0, %1" : "=v"(dst[i]) : "s"(src[i]));
 }
 
-// Cooley-Tukey butterfly with lazy reduction (Harvey, "Faster arithmetic for
-// number-theoretic transforms", J. Symb. Comp. 2014): inputs and outputs in
-// [0, 4q), twiddle w < q in Montgomery form, q2 = 2q.
-//   x <- x mod 2q;  t <- w*y in [0, 2q);  x' = x + t;  y' = x - t + 2q.
-// Same residues as (x + wy, x - wy) mod q; 5L add-class ops instead of 8L.
-template <int L>
-__device__ __forceinline__ void ct_butterfly_lazy(u32* x, u32* y, const u32* w, const u32* q, const u32* q2,
-                                                  u32 qinv) {
-  u32 xr[L], t[L], d[L];
-  reduce_once<L>(xr, x, q2);
-  mont_mul_lazy<L>(t, y, w, q, qinv);
-  add_vv<L>(x, xr, t);
-  sub_vv<L>(d, xr, t);
-  add_vs<L>(y, d, q2);
-}
-
 // Lazy butterfly with twiddle 1 (the first stages of a transform): the same
 // residues as the multiplying butterfly, with t = y mod 2q in [0, 2q) in place
 // of the Montgomery product w*y.
@@ -557,35 +618,12 @@ __device__ __forceinline__ void ct_butterfly_one(u32* x, u32* y, const u32* q2v)
   add_vv<L>(y, d, q2v);
 }
 
-// Lazy butterfly with the twiddle in digit form (mont_mul_digits) and 2q in VGPRs.
-template <int L>
-__device__ __forceinline__ void ct_butterfly_digits(u32* x, u32* y, const u32* wd, const u32* qd, u32 qinvd,
-                                                    const u32* q2v) {
-  u32 xr[L], t[L], d[L], s[L];
-  u64 br = sub_vv<L>(s, x, q2v);  // x - 2q; borrow <=> x < 2q
-  select<L>(xr, br, x, s);
-  mont_mul_digits<L>(t, y, wd, qd, qinvd);
-  add_vv<L>(x, xr, t);
-  sub_vv<L>(d, xr, t);
-  add_vv<L>(y, d, q2v);
-}
-
-// The same butterfly with 2q already in VGPRs (q2v); q stays uniform for the
-// multiply's products.
-template <int L>
-__device__ __forceinline__ void ct_butterfly_lazy_v(u32* x, u32* y, const u32* w, const u32* q, const u32* q2v,
-                                                    u32 qinv) {
-  u32 xr[L], t[L], d[L], s[L];
-  u64 br = sub_vv<L>(s, x, q2v);  // x - 2q; borrow <=> x < 2q
-  select<L>(xr, br, x, s);
-  mont_mul_lazy<L>(t, y, w, q, qinv);
-  add_vv<L>(x, xr, t);
-  sub_vv<L>(d, xr, t);
-  add_vv<L>(y, d, q2v);
-}
-
-// The additions of the lazy butterfly once its product t = w*y in [0, 2q) is
-// known: x <- x mod 2q; y = x - t + 2q; x = x + t.
+// Cooley-Tukey butterfly with lazy reduction (Harvey, "Faster arithmetic for
+// number-theoretic transforms", J. Symb. Comp. 2014): inputs and outputs in
+// [0, 4q), q2 = 2q.
+//   x <- x mod 2q;  t <- w*y in [0, 2q);  x' = x + t;  y' = x - t + 2q.
+// Same residues as (x + wy, x - wy) mod q; 5L add-class ops instead of 8L.
+// Here the additions, once the product t = w*y in [0, 2q) is known.
 template <int L>
 __device__ __forceinline__ void ct_lazy_tail(u32* x, u32* y, const u32* t, const u32* q2v) {
   u32 xr[L], d[L], s[L];
@@ -594,6 +632,24 @@ __device__ __forceinline__ void ct_lazy_tail(u32* x, u32* y, const u32* t, const
   add_vv<L>(x, xr, t);
   sub_vv<L>(d, xr, t);
   add_vv<L>(y, d, q2v);
+}
+
+// Lazy butterfly with the twiddle and its quotient in digits, 2q in VGPRs.
+template <int L>
+__device__ __forceinline__ void ct_butterfly_digits(u32* x, u32* y, const u32* w, const u32* wq, const u32* nqd,
+                                                    const u32* q2v) {
+  u32 t[L];
+  quot_mul<L>(t, y, w, wq, nqd);
+  ct_lazy_tail<L>(x, y, t, q2v);
+}
+
+// The same with the Karatsuba form of the product w y.
+template <int L>
+__device__ __forceinline__ void ct_butterfly_kara(u32* x, u32* y, const u32* w, const u32* wq, const u32* nqd,
+                                                  const u32* q2v) {
+  u32 t[L];
+  quot_mul_kara<L>(t, y, w, wq, nqd);
+  ct_lazy_tail<L>(x, y, t, q2v);
 }
 
 // The same for a full-width modulus: t (with its carry word) reduced, then

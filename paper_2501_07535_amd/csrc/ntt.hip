@@ -29,11 +29,11 @@ uint32_t ntt_max_threads(int L, uint32_t radix_log) {
   return live <= 16 ? 1024u : (live <= 32 ? 512u : 256u);
 }
 
-int launch_ntt_pass(const FieldRaw& f, const DigitConsts& dc, const NttPassArgs& a, const NttConsts& c,
+int launch_ntt_pass(const FieldRaw& f, const DigitConsts& dc, const NttPassArgs& a,
                     uint32_t threads, uint64_t tiles, uint32_t radix_log, uint32_t kara, hipStream_t s) {
   switch (f.L) {
 #define CASE(LL) \
-  case LL: return launch_pass_L<LL>(f, dc, a, c, threads, tiles, radix_log, kara, s);
+  case LL: return launch_pass_L<LL>(f, dc, a, threads, tiles, radix_log, kara, s);
     MOMA_FOR_EACH_L(CASE)
 #undef CASE
   }
@@ -78,15 +78,15 @@ size_t ntt_consts_bytes(int L, bool fw) {
   return 0;
 }
 
-void ntt_fill_consts(const FieldRaw& f, const DigitConsts& dc, const NttConsts* nc, void* dst) {
+void ntt_fill_consts(const FieldRaw& f, const DigitConsts& dc, void* dst) {
   switch (f.L) {
 #define CASE(LL)                                          \
   case LL: {                                              \
     if (f.fw) {                                           \
-      NttC<LL, true> c = make_consts<LL, true>(f, dc, nc); \
+      NttC<LL, true> c = make_consts<LL, true>(f, dc);     \
       memcpy(dst, &c, sizeof(c));                         \
     } else {                                              \
-      NttC<LL> c = make_consts<LL>(f, dc, nc);            \
+      NttC<LL> c = make_consts<LL>(f, dc);                \
       memcpy(dst, &c, sizeof(c));                         \
     }                                                     \
     return;                                               \

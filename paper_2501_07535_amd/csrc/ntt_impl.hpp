@@ -21,9 +21,9 @@
 //   * Inside a tile, each thread runs radix-2^r units in registers: 2^r
 //     elements spanning r consecutive stages, so LDS is read and written, and
 //     the workgroup synchronised, once per r stages instead of once per stage.
-//   * Twiddle table: entry m + i' (m = 2^s) holds w_{2m}^{i'} in Montgomery form
-//     for R = 2^(bD), as D b-bit digits padded to an even word count (level s
-//     stores the first m powers of w_{2m}).  With that order the C
+//   * Twiddle table: entry m + i' (m = 2^s) holds w_{2m}^{i'} and its quotient
+//     floor(w_{2m}^{i'} 2^(bD) / q), D b-bit digits each (level s stores the
+//     first m powers of w_{2m}).  With that order the C
 //     groups of a tile read C consecutive entries, and the first pass reads a
 //     table prefix shared by every tile.
 // Butterflies use lazy reduction: values stay in [0, 4q) between stages and
@@ -44,50 +44,38 @@ struct NttC {
   u32 q[L];
   u32 q2[L];                        // 2q (unused for a full-width modulus)
   u32 qinv;
-  u32 nscaled[Digits<L, FW>::D];    // last-pass scale of the inverse, digit Montgomery form
-  u32 qd[Digits<L, FW>::D];         // q in b-bit digits (twiddle multiply)
+  u32 nqd[Digits<L, FW>::D];        // 2^(bD) - q in b-bit digits (twiddle multiply)
+  u32 qd[Digits<L, FW>::D];         // q in b-bit digits (pointwise product)
   u32 qinvd;                        // -q^-1 mod 2^b
 };
 
 __device__ __forceinline__ u32 rev_bits(u32 x, u32 b) { return b ? (__brev(x) >> (32 - b)) : 0u; }
 
-template <int L>
-__device__ __forceinline__ void load_entry(u32* r, const u32* __restrict__ p) {
-  if constexpr (L % 4 == 0) {
-    const uint4* v = reinterpret_cast<const uint4*>(p);
-#pragma unroll
-    for (int i = 0; i < L / 4; i++) {
-      uint4 t = v[i];
-      r[4 * i] = t.x;
-      r[4 * i + 1] = t.y;
-      r[4 * i + 2] = t.z;
-      r[4 * i + 3] = t.w;
-    }
-  } else if constexpr (L % 2 == 0) {
-    const uint2* v = reinterpret_cast<const uint2*>(p);
-#pragma unroll
-    for (int i = 0; i < L / 2; i++) {
-      uint2 t = v[i];
-      r[2 * i] = t.x;
-      r[2 * i + 1] = t.y;
-    }
-  } else {
-#pragma unroll
-    for (int i = 0; i < L; i++) r[i] = p[i];
-  }
-}
-
-// one twiddle entry: digit_stride(L, FW) words, 8-byte aligned
+// One twiddle: its quotient's digits, then its own, tw_words(L, FW) words.  The
+// table holds them in 16-byte pieces, piece c of entry e at word 4 (c n + e):
+// the lanes of a load read consecutive pieces, whatever the entry's length.
+// `first` (the level's first entry plus the unit's, uniform) and the lane's
+// offset `off` < 2^25 entries keep the lane's part of the address in 32 bits.
 template <int L, bool FW = false>
-__device__ __forceinline__ void load_digits(u32* r, const u32* __restrict__ p) {
-  const uint2* v = reinterpret_cast<const uint2*>(p);
+struct Twiddle {
+  static constexpr int D = Digits<L, FW>::D;
+  u32 v[tw_words(L, FW)];
+  __device__ __forceinline__ const u32* wq() const { return v; }
+  __device__ __forceinline__ const u32* w() const { return v + D; }
+  __device__ __forceinline__ void load(const u32* __restrict__ tw, u64 n, u64 first, u32 off) {
+    // (opaque here, or the bases of a whole round are computed ahead of it and
+    // spilled)
+    asm volatile("" : "+s"(first));
 #pragma unroll
-  for (int i = 0; i < digit_stride(L, FW) / 2; i++) {
-    uint2 t = v[i];
-    r[2 * i] = t.x;
-    r[2 * i + 1] = t.y;
+    for (int i = 0; i < tw_words(L, FW) / 4; i++) {
+      const uint4 t = uniform_at<uint4>(tw + 4 * (i * n + first), off << 4);
+      v[4 * i] = t.x;
+      v[4 * i + 1] = t.y;
+      v[4 * i + 2] = t.z;
+      v[4 * i + 3] = t.w;
+    }
   }
-}
+};
 
 // Tile geometry shared by the load, compute and store phases.
 struct TileGeo {
@@ -95,10 +83,70 @@ struct TileGeo {
   u64 n, S, o0, ro, b0;
 };
 
-// twiddle table position for local stage sg, local block lb of group g
-__device__ __forceinline__ u64 tw_pos(const TileGeo& t, u32 sg, u32 lb, u32 g) {
-  return (t.K == 0) ? ((1ull << sg) + rev_bits(lb, sg))
-                    : ((1ull << (t.K + sg)) + ((u64)rev_bits(lb, sg) << t.K) + t.b0 + g);
+// Twiddle of local stage sg, local block lb of group g: table entry
+// 2^(K+sg) + rev_sg(lb) 2^K + (b0 + g when K > 0).  For a unit that starts at
+// stage sg0 in block lb, stage sg0 + s and sub-block i < 2^s this is the
+// unit's own offset plus a uniform 2^(K+sg0+s) + rev_s(i) 2^(K+sg0).
+__device__ __forceinline__ u32 tw_off(const TileGeo& t, u32 sg0, u32 lb, u32 g) {
+  const u32 r = (__brev(lb) >> 1) >> (31 - sg0);  // lb < 2^sg0
+  return (r << t.K) + (t.K == 0 ? 0u : (u32)t.b0 + g);
+}
+__device__ __forceinline__ u64 tw_first(const TileGeo& t, u32 sg0, u32 s, u32 i) {
+  return (1ull << (t.K + sg0 + s)) + ((u64)rev_bits(i, s) << (t.K + sg0));
+}
+
+// A tile in LDS: element idx = row * C + group, its limbs in planes of 16-byte
+// quads, then an 8-byte pair and a single word as L leaves them (4 L E bytes in
+// all).  An element then takes L / 4 LDS instructions and addresses each way
+// instead of L, and lanes with consecutive groups still access consecutive
+// banks.  (In limb planes of single words a stage of a 256-bit radix-2 unit
+// spent a third of its time on LDS: about 500 cycles until its elements were in,
+// against 1340 for the butterfly; 2^12 points took 20.8 us, with quads 18.6.)
+template <int L>
+__device__ __forceinline__ void lds_get(u32* x, const u32* lds, u32 E, u32 idx) {
+#pragma unroll
+  for (int q = 0; q < L / 4; q++) {
+    const uint4 v = *reinterpret_cast<const uint4*>(lds + 4 * (q * E + idx));
+    x[4 * q] = v.x;
+    x[4 * q + 1] = v.y;
+    x[4 * q + 2] = v.z;
+    x[4 * q + 3] = v.w;
+  }
+  if constexpr (L % 4 >= 2) {
+    const uint2 v = *reinterpret_cast<const uint2*>(lds + 4 * (L / 4) * E + 2 * idx);
+    x[L / 4 * 4] = v.x;
+    x[L / 4 * 4 + 1] = v.y;
+  }
+  if constexpr (L % 2) x[L - 1] = lds[(L - 1) * E + idx];
+}
+template <int L>
+__device__ __forceinline__ void lds_put(u32* lds, u32 E, u32 idx, const u32* x) {
+#pragma unroll
+  for (int q = 0; q < L / 4; q++)
+    *reinterpret_cast<uint4*>(lds + 4 * (q * E + idx)) = make_uint4(x[4 * q], x[4 * q + 1], x[4 * q + 2], x[4 * q + 3]);
+  if constexpr (L % 4 >= 2)
+    *reinterpret_cast<uint2*>(lds + 4 * (L / 4) * E + 2 * idx) = make_uint2(x[L / 4 * 4], x[L / 4 * 4 + 1]);
+  if constexpr (L % 2) lds[(L - 1) * E + idx] = x[L - 1];
+}
+
+// Element e of a radix-2^R unit in HBM: the lane's part of its word offset
+// (element 0: row p0 of group g) and the uniform rest.  Row u lies at u S + o0 + g
+// in the first pass's input and at (ro, rev_k(u), b0 + g) after it; the unit's
+// rows are e 2^(k-sg0-R) apart, and e's bits reverse to rev_R(e) 2^sg0.
+__device__ __forceinline__ u32 row_off(const TileGeo& t, u32 u, u32 g, bool natural) {
+  return natural ? u * (u32)t.S + (u32)t.o0 + g
+                 : (u32)(t.ro << (t.K + t.k)) + ((__brev(u) >> (32 - t.k)) << t.K) + (u32)t.b0 + g;
+}
+// one element's limbs from / to plane 0's word `first` (uniform) plus the lane's
+template <int L>
+__device__ __forceinline__ void hbm_get(u32* x, const u32* first, u64 n, u32 lane_bytes) {
+#pragma unroll
+  for (int j = 0; j < L; j++, first += n) x[j] = uniform_at<u32>(first, lane_bytes);
+}
+template <int L>
+__device__ __forceinline__ void hbm_put(const u32* x, u32* first, u64 n, u32 lane_bytes) {
+#pragma unroll
+  for (int j = 0; j < L; j++, first += n) uniform_put<u32>(first, lane_bytes, x[j]);
 }
 
 // One round of R stages [sg0, sg0+R) on every radix-2^R unit of the tile.
@@ -111,25 +159,39 @@ __device__ __forceinline__ u64 tw_pos(const TileGeo& t, u32 sg, u32 lb, u32 g) {
 // addresses (the rows of one column are consecutive across lanes, so every
 // store instruction covers 64-byte runs) instead of back to LDS, so the pass
 // has no separate store phase and the stores drain while other units compute.
-template <int L, bool FW = false>
-__device__ __forceinline__ void finish_elem(u32* x, const NttPassArgs& a, const NttC<L, FW>& c) {
-  if constexpr (FW) {
-    // values are canonical throughout; only the inverse's scale remains
-    if (a.last && a.scale) {
+// What the last pass does to its N elements before it stores them.  The
+// inverse's factor is read here, by uniform loads, and not held in registers
+// from the kernel's start.
+template <int L, bool FW, int N>
+__device__ __forceinline__ void finish_elems(u32 (*x)[L], const NttPassArgs& a, const NttC<L, FW>& c) {
+  if (!a.last) return;
+  if (a.scale) {
+    constexpr int D = Digits<L, FW>::D;
+    typedef const __attribute__((address_space(4))) u32* ConstWords;
+    u64 p = (u64)a.scale;
+    asm volatile("" : "+s"(p));
+    u32 sq[D], sd[D];
+#pragma unroll
+    for (int i = 0; i < D; i++) {
+      sq[i] = ((ConstWords)p)[i];
+      sd[i] = ((ConstWords)p)[D + i];
+    }
+#pragma unroll
+    for (int e = 0; e < N; e++) {
       u32 y[L], top;
-      mont_mul_digits<L, true>(y, x, c.nscaled, c.qd, c.qinvd, &top);
-      reduce_top<L>(x, y, top, c.q);
+      quot_mul<L, FW>(y, x[e], sd, sq, c.nqd, &top);  // x < 4q (q, full width): y in [0, 2q)
+      if constexpr (FW)
+        reduce_top<L>(x[e], y, top, c.q);
+      else
+        reduce_once<L>(x[e], y, c.q);
     }
-    return;
-  }
-  if (a.last) {
-    u32 y[L];
-    if (a.scale) {
-      mont_mul_digits<L>(y, x, c.nscaled, c.qd, c.qinvd);  // x < 4q, scale < q: y in [0, 2q)
-    } else {
-      reduce_once<L>(y, x, c.q2);                           // [0, 4q) -> [0, 2q)
+  } else if constexpr (!FW) {  // (full-width values are canonical throughout)
+#pragma unroll
+    for (int e = 0; e < N; e++) {
+      u32 y[L];
+      reduce_once<L>(y, x[e], c.q2);  // [0, 4q) -> [0, 2q)
+      reduce_once<L>(x[e], y, c.q);   // -> [0, q)
     }
-    reduce_once<L>(x, y, c.q);                              // -> [0, q)
   }
 }
 
@@ -158,11 +220,8 @@ __device__ __forceinline__ void round_late(u32* lds, const TileGeo& t, u32 sg0, 
     u32 x[L], y[L];
     if (FIRST && lb == 0) {
       // twiddle 1: no multiply
-#pragma unroll
-      for (int j = 0; j < L; j++) {
-        x[j] = lds[(j * t.rows + r0) * t.C + g];
-        y[j] = lds[(j * t.rows + r1) * t.C + g];
-      }
+      lds_get<L>(x, lds, t.E, r0 * t.C + g);
+      lds_get<L>(y, lds, t.E, r1 * t.C + g);
       u32 qv[L];
       to_vgprs<L>(qv, FW ? c.q : c.q2);
       if constexpr (FW)
@@ -170,18 +229,17 @@ __device__ __forceinline__ void round_late(u32* lds, const TileGeo& t, u32 sg0, 
       else
         ct_butterfly_one<L>(x, y, qv);
     } else {
-      u32 w[digit_stride(L, FW)], p[L], top = 0;
-      load_digits<L, FW>(w, tw + tw_pos(t, sg0, lb, g) * digit_stride(L, FW));
-#pragma unroll
-      for (int j = 0; j < L; j++) y[j] = lds[(j * t.rows + r1) * t.C + g];
+      Twiddle<L, FW> w;
+      u32 p[L], top = 0;
+      w.load(tw, t.n, tw_first(t, sg0, 0, 0), tw_off(t, sg0, lb, g));
+      lds_get<L>(y, lds, t.E, r1 * t.C + g);
       if constexpr (FW)
-        mont_mul_digits<L, true>(p, y, w, c.qd, c.qinvd, &top);
+        quot_mul<L, true>(p, y, w.w(), w.wq(), c.nqd, &top);
       else if constexpr (AR == kArithKara)
-        mont_mul_digits_kara<L>(p, y, w, c.qd, c.qinvd);
+        quot_mul_kara<L>(p, y, w.w(), w.wq(), c.nqd);
       else
-        mont_mul_digits<L>(p, y, w, c.qd, c.qinvd);
-#pragma unroll
-      for (int j = 0; j < L; j++) x[j] = lds[(j * t.rows + r0) * t.C + g];
+        quot_mul<L>(p, y, w.w(), w.wq(), c.nqd);
+      lds_get<L>(x, lds, t.E, r0 * t.C + g);
       u32 qv[L];
       to_vgprs<L>(qv, FW ? c.q : c.q2);
       if constexpr (FW)
@@ -190,21 +248,14 @@ __device__ __forceinline__ void round_late(u32* lds, const TileGeo& t, u32 sg0, 
         ct_lazy_tail<L>(x, y, p, qv);
     }
     if constexpr (STORE) {
-      const u64 base = (t.ro << (t.K + k)) + t.b0 + g;
-      finish_elem<L, FW>(x, a, c);
-      finish_elem<L, FW>(y, a, c);
-      const u64 d0 = base + ((u64)rev_bits(r0, k) << t.K), d1 = base + ((u64)rev_bits(r1, k) << t.K);
-#pragma unroll
-      for (int j = 0; j < L; j++) {
-        a.out[(u64)j * t.n + d0] = x[j];
-        a.out[(u64)j * t.n + d1] = y[j];
-      }
+      const u32 dst = row_off(t, r0, g, false) << 2;
+      finish_elems<L, FW, 1>(&x, a, c);
+      finish_elems<L, FW, 1>(&y, a, c);
+      hbm_put<L>(x, a.out, t.n, dst);
+      hbm_put<L>(y, a.out + (1ull << (t.K + sg0)), t.n, dst);
     } else {
-#pragma unroll
-      for (int j = 0; j < L; j++) {
-        lds[(j * t.rows + r0) * t.C + g] = x[j];
-        lds[(j * t.rows + r1) * t.C + g] = y[j];
-      }
+      lds_put<L>(lds, t.E, r0 * t.C + g, x);
+      lds_put<L>(lds, t.E, r1 * t.C + g, y);
     }
   }
 }
@@ -230,72 +281,59 @@ __device__ __forceinline__ void ntt_round(u32* lds, const TileGeo& t, u32 sg0, c
     u32 lb = v >> (k - sg0 - R);
     u32 p0 = lb * B + (v & (sub - 1));
     u32 x[1 << R][L];
+    const u32 idx0 = p0 * t.C + g, step = sub << t.logc;  // the unit's elements in LDS
     // LOADG: the first stage's twiddle (one per unit) is loaded before the
     // elements, and the elements pair by pair of the first stage, (e, e +
     // 2^(R-1)): a wave's loads complete in issue order, so the first pair's
     // butterfly can start while the later pairs are still in flight
-    u32 w0[LOADG ? digit_stride(L, FW) : 1];
+    const u32 toff = tw_off(t, sg0, lb, g);
+    Twiddle<L, FW> w;
     if constexpr (LOADG) {
-      if constexpr (!FIRST) load_digits<L, FW>(w0, tw + tw_pos(t, sg0, lb, g) * digit_stride(L, FW));
+      if constexpr (!FIRST) w.load(tw, t.n, tw_first(t, sg0, 0, 0), toff);
+      const u32 src = row_off(t, p0, g, t.K == 0) << 2;
 #pragma unroll
       for (int pp = 0; pp < (1 << R); pp++) {
         const int e = (pp >> 1) + (pp & 1) * (1 << (R - 1));
-        const u32 u = p0 + e * sub;  // LDS row; global row u (first pass) or rev(u) (later passes)
-        const u64 src = (t.K == 0) ? (u64)u * t.S + t.o0 + g
-                                   : (t.ro << (t.K + k)) + ((u64)rev_bits(u, k) << t.K) + t.b0 + g;
-#pragma unroll
-        for (int j = 0; j < L; j++) x[e][j] = a.in[(u64)j * t.n + src];
+        const u64 first = t.K == 0 ? (u64)(e * sub) * t.S : (u64)rev_bits(e, R) << (t.K + sg0);
+        hbm_get<L>(x[e], a.in + first, t.n, src);
       }
     } else {
 #pragma unroll
-      for (int e = 0; e < (1 << R); e++)
-#pragma unroll
-        for (int j = 0; j < L; j++) x[e][j] = lds[(j * t.rows + p0 + e * sub) * t.C + g];
+      for (int e = 0; e < (1 << R); e++) lds_get<L>(x[e], lds, t.E, idx0 + e * step);
     }
 #pragma unroll
     for (int s = 0; s < R; s++) {
-      const int kb = R - 1 - s, half = 1 << kb;
+      const int half = 1 << (R - 1 - s);
+      // block i of the 2^s the unit has at this stage: one twiddle, `half` pairs (e, e + half)
 #pragma unroll
-      for (int p = 0; p < (1 << (R - 1)); p++) {
-        // p with a zero bit inserted at position kb: the pair (e, e + half) of this stage
-        const int e = ((p >> kb) << (kb + 1)) | (p & (half - 1));
-        auto bfly = [&](const u32* w) {
-          if constexpr (FW)
-            ct_butterfly_fw<L>(x[e], x[e + half], w, c.qd, c.qinvd, q2v);
-          else if constexpr (AR == kArithKara)
-            ct_butterfly_kara<L>(x[e], x[e + half], w, c.qd, c.qinvd, q2v);
-          else
-            ct_butterfly_digits<L>(x[e], x[e + half], w, c.qd, c.qinvd, q2v);
-        };
-        if (FIRST && (e >> (R - s)) == 0) {
-          if constexpr (FW)
-            ct_butterfly_one_fw<L>(x[e], x[e + half], q2v);
-          else
-            ct_butterfly_one<L>(x[e], x[e + half], q2v);
-        } else if (LOADG && s == 0) {
-          bfly(w0);  // stage 0: every pair of the unit has block lb
-        } else {
-          u32 lbk = (lb << s) + (u32)(e >> (R - s));
-          u32 w[digit_stride(L, FW)];
-          load_digits<L, FW>(w, tw + tw_pos(t, sg0 + s, lbk, g) * digit_stride(L, FW));
-          bfly(w);
+      for (int i = 0; i < (1 << s); i++) {
+        const bool one = FIRST && i == 0;
+        if (!one && !(LOADG && s == 0)) w.load(tw, t.n, tw_first(t, sg0, s, i), toff);
+#pragma unroll
+        for (int e = 2 * half * i; e < 2 * half * i + half; e++) {
+          if (one) {
+            if constexpr (FW)
+              ct_butterfly_one_fw<L>(x[e], x[e + half], q2v);
+            else
+              ct_butterfly_one<L>(x[e], x[e + half], q2v);
+          } else if constexpr (FW) {
+            ct_butterfly_fw<L>(x[e], x[e + half], w.w(), w.wq(), c.nqd, q2v);
+          } else if constexpr (AR == kArithKara) {
+            ct_butterfly_kara<L>(x[e], x[e + half], w.w(), w.wq(), c.nqd, q2v);
+          } else {
+            ct_butterfly_digits<L>(x[e], x[e + half], w.w(), w.wq(), c.nqd, q2v);
+          }
         }
       }
     }
     if constexpr (STORE) {
-      const u64 base = (t.ro << (t.K + k)) + t.b0 + g;
+      const u32 dst = row_off(t, p0, g, false) << 2;
+      finish_elems<L, FW, (1 << R)>(x, a, c);
 #pragma unroll
-      for (int e = 0; e < (1 << R); e++) {
-        const u64 dst = base + ((u64)rev_bits(p0 + e * sub, k) << t.K);
-        finish_elem<L, FW>(x[e], a, c);
-#pragma unroll
-        for (int j = 0; j < L; j++) a.out[(u64)j * t.n + dst] = x[e][j];
-      }
+      for (int e = 0; e < (1 << R); e++) hbm_put<L>(x[e], a.out + ((u64)rev_bits(e, R) << (t.K + sg0)), t.n, dst);
     } else {
 #pragma unroll
-      for (int e = 0; e < (1 << R); e++)
-#pragma unroll
-        for (int j = 0; j < L; j++) lds[(j * t.rows + p0 + e * sub) * t.C + g] = x[e][j];
+      for (int e = 0; e < (1 << R); e++) lds_put<L>(lds, t.E, idx0 + e * step, x[e]);
     }
   }
 }
@@ -342,21 +380,21 @@ __device__ __forceinline__ void ntt_round_last(u32* lds, const TileGeo& t, u32 s
     u32 g = b & (t.C - 1), v = b >> t.logc;
     u32 lb = v >> 1;
     u32 p0 = lb * B + (v & 1u);
+    const u32 toff = tw_off(t, sg0, lb, g);
     u32 x[1 << R][L];
+    const u32 step = 2u << t.logc;
 #pragma unroll
-    for (int e = 0; e < (1 << R); e++)
-#pragma unroll
-      for (int j = 0; j < L; j++) x[e][j] = lds[(j * t.rows + p0 + 2 * e) * t.C + g];
+    for (int e = 0; e < (1 << R); e++) lds_get<L>(x[e], lds, t.E, p0 * t.C + g + e * step);
+    Twiddle<L> w;
 #pragma unroll
     for (int s = 0; s < R; s++) {
-      const int kb = R - 1 - s, half = 1 << kb;
+      const int half = 1 << (R - 1 - s);
 #pragma unroll
-      for (int p = 0; p < (1 << (R - 1)); p++) {
-        const int e = ((p >> kb) << (kb + 1)) | (p & (half - 1));
-        u32 lbk = (lb << s) + (u32)(e >> (R - s));
-        u32 w[digit_stride(L)];
-        load_digits<L>(w, tw + tw_pos(t, sg0 + s, lbk, g) * digit_stride(L));
-        ct_butterfly_digits<L>(x[e], x[e + half], w, c.qd, c.qinvd, q2v);
+      for (int i = 0; i < (1 << s); i++) {
+        w.load(tw, t.n, tw_first(t, sg0, s, i), toff);
+#pragma unroll
+        for (int e = 2 * half * i; e < 2 * half * i + half; e++)
+          ct_butterfly_digits<L>(x[e], x[e + half], w.w(), w.wq(), c.nqd, q2v);
       }
     }
 #pragma unroll
@@ -366,38 +404,30 @@ __device__ __forceinline__ void ntt_round_last(u32* lds, const TileGeo& t, u32 s
     const u32 h = v & 1u;
 #pragma unroll
     for (int jp = 0; jp < H; jp++) {
-      u32 lbk = (lb << R) + (h << (R - 1)) + (u32)jp;
-      u32 w[digit_stride(L)];
-      load_digits<L>(w, tw + tw_pos(t, k - 1, lbk, g) * digit_stride(L));
-      ct_butterfly_digits<L>(x[jp], x[jp + H], w, c.qd, c.qinvd, q2v);
+      // last-stage block 2^R lb + 2^(R-1) h + jp: h reverses to the lowest bit
+      w.load(tw, t.n, tw_first(t, sg0, R, (u32)jp), toff + (h << (t.K + sg0)));
+      ct_butterfly_digits<L>(x[jp], x[jp + H], w.w(), w.wq(), c.nqd, q2v);
     }
     const u32 r0 = lb * B + (h << R);
     if constexpr (STORE) {
-      const u64 base = (t.ro << (t.K + k)) + t.b0 + g;
-#pragma unroll
-      for (int jp = 0; jp < H; jp++)
-#pragma unroll
-        for (int o = 0; o < 2; o++) {
-          u32* y = x[jp + o * H];
-          const u64 dst = base + ((u64)rev_bits(r0 + 2 * jp + o, k) << t.K);
-          finish_elem<L>(y, a, c);
-#pragma unroll
-          for (int j = 0; j < L; j++) a.out[(u64)j * t.n + dst] = y[j];
-        }
-    } else {
+      // row r0 + 2 jp + o: its low R bits reverse to the top of the k
+      const u32 dst = row_off(t, r0, g, false) << 2;
+      finish_elems<L, false, (1 << R)>(x, a, c);
 #pragma unroll
       for (int jp = 0; jp < H; jp++)
 #pragma unroll
         for (int o = 0; o < 2; o++)
+          hbm_put<L>(x[jp + o * H], a.out + ((u64)rev_bits(2 * jp + o, R) << (t.K + sg0 + 1)), t.n, dst);
+    } else {
 #pragma unroll
-          for (int j = 0; j < L; j++) lds[(j * t.rows + r0 + 2 * jp + o) * t.C + g] = x[jp + o * H][j];
+      for (int jp = 0; jp < H; jp++)
+#pragma unroll
+        for (int o = 0; o < 2; o++) lds_put<L>(lds, t.E, (r0 + 2 * jp + o) * t.C + g, x[jp + o * H]);
     }
   }
 }
 
 // One tile of one pass: stages [K, K+k) on C = 2^logc groups of 2^k elements.
-// LDS holds the tile limb-planar: word (j * 2^k + u) * C + g is limb j of row u
-// of group g, so lanes with consecutive g touch consecutive banks.
 // the fused store keeps a unit's finished elements live while it stores them
 // (up to 10 limbs, 9 for a full-width modulus: at 11 to 16 limbs it measured
 // no faster than the store from LDS)
@@ -468,95 +498,55 @@ __device__ __forceinline__ void pass_tile(u32* lds, const NttPassArgs& a, const 
   const bool direct = LASTX && !MUL && a.direct != 0;
 
   // ---- load (natural order in the first pass, bit-reversed storage after).
-  // Each lane moves 4 consecutive words per limb: 4 groups of one row when the
-  // tile has C >= 4 groups, else 4 consecutive rows of a one-pass transform.
+  // Up to 8 limbs each lane moves 4 consecutive words per limb: 4 groups of one
+  // row when the tile has C >= 4 groups, else 4 consecutive rows of a one-pass
+  // transform; wider limbs (4 L live words) take one element per lane.
   const bool vec_g = t.C >= 4, vec_u = (t.C == 1 && t.S == 1 && t.rows >= 4);
   if (direct) {
     // the first round loads its own elements
-  } else if (vec_g || vec_u) {
+  } else if (L <= 8 && (vec_g || vec_u)) {
     for (u32 e4 = tid; e4 < (t.E >> 2); e4 += T) {
-      u32 e = e4 << 2;
-      u32 g = e & (t.C - 1), v = e >> t.logc;
-      u64 src;
-      u32 u;
-      if (t.K == 0) {
-        u = v;
-        src = (u64)u * t.S + t.o0 + g;
-      } else {
-        u = rev_bits(v, t.k);
-        src = (t.ro << (t.K + t.k)) + ((u64)v << t.K) + t.b0 + g;
+      const u32 e = e4 << 2, g = e & (t.C - 1), v = e >> t.logc;
+      const u32 u = t.K == 0 ? v : rev_bits(v, t.k);
+      const u64 src = t.K == 0 ? (u64)u * t.S + t.o0 + g : (t.ro << (t.K + t.k)) + ((u64)v << t.K) + t.b0 + g;
+      u32 x[4][L];
+#pragma unroll
+      for (int j = 0; j < L; j++) {
+        const uint4 w = *reinterpret_cast<const uint4*>(a.in + (u64)j * n + src);
+        x[0][j] = w.x; x[1][j] = w.y; x[2][j] = w.z; x[3][j] = w.w;
       }
-      if constexpr (MUL && L <= 8) {
-        // 4 elements of each input in registers, multiplied pointwise
-        u32 x[4][L], y[4][L];
+      if constexpr (MUL) {
+        u32 y[4][L], r[4][L];
 #pragma unroll
         for (int j = 0; j < L; j++) {
-          uint4 w = *reinterpret_cast<const uint4*>(a.in + (u64)j * n + src);
-          uint4 z = *reinterpret_cast<const uint4*>(a.in2 + (u64)j * n + src);
-          x[0][j] = w.x; x[1][j] = w.y; x[2][j] = w.z; x[3][j] = w.w;
+          const uint4 z = *reinterpret_cast<const uint4*>(a.in2 + (u64)j * n + src);
           y[0][j] = z.x; y[1][j] = z.y; y[2][j] = z.z; y[3][j] = z.w;
         }
-        u32 r[4][L];
 #pragma unroll
         for (int q4 = 0; q4 < 4; q4++) pointwise_digits<L, FW>(r[q4], x[q4], y[q4], c);
 #pragma unroll
-        for (int j = 0; j < L; j++)
-          *reinterpret_cast<uint4*>(lds + (j * t.rows + u) * t.C + g) = make_uint4(r[0][j], r[1][j], r[2][j], r[3][j]);
-      } else if constexpr (MUL) {
-        // wider limbs, fewer live registers: stage the first input in LDS as
-        // the plain load does, then multiply one element at a time; each lane
-        // rereads only the 4 consecutive LDS words (4 groups of one row, or 4
-        // rows when C == 1) that it wrote itself
-#pragma unroll
-        for (int j = 0; j < L; j++) {
-          uint4 w = *reinterpret_cast<const uint4*>(a.in + (u64)j * n + src);
-          *reinterpret_cast<uint4*>(lds + (j * t.rows + u) * t.C + g) = w;
-        }
-#pragma unroll 1
-        for (u32 q4 = 0; q4 < 4; q4++) {
-          u32 x[L], y[L], r[L];
-#pragma unroll
-          for (int j = 0; j < L; j++) {
-            x[j] = lds[(j * t.rows + u) * t.C + g + q4];
-            y[j] = a.in2[(u64)j * n + src + q4];
-          }
-          pointwise_digits<L, FW>(r, x, y, c);
-#pragma unroll
-          for (int j = 0; j < L; j++) lds[(j * t.rows + u) * t.C + g + q4] = r[j];
-        }
+        for (int q4 = 0; q4 < 4; q4++) lds_put<L>(lds, t.E, u * t.C + g + q4, r[q4]);
       } else {
 #pragma unroll
-        for (int j = 0; j < L; j++) {
-          uint4 w = *reinterpret_cast<const uint4*>(a.in + (u64)j * n + src);
-          *reinterpret_cast<uint4*>(lds + (j * t.rows + u) * t.C + g) = w;
-        }
+        for (int q4 = 0; q4 < 4; q4++) lds_put<L>(lds, t.E, u * t.C + g + q4, x[q4]);
       }
     }
   } else {
     for (u32 e = tid; e < t.E; e += T) {
-      u32 g = e & (t.C - 1), v = e >> t.logc;
-      u64 src;
-      u32 u;
-      if (t.K == 0) {
-        u = v;
-        src = (u64)u * t.S + t.o0 + g;
-      } else {
-        u = rev_bits(v, t.k);
-        src = (t.ro << (t.K + t.k)) + ((u64)v << t.K) + t.b0 + g;
-      }
+      const u32 g = e & (t.C - 1), v = e >> t.logc;
+      const u32 u = t.K == 0 ? v : rev_bits(v, t.k);
+      const u64 src = t.K == 0 ? (u64)u * t.S + t.o0 + g : (t.ro << (t.K + t.k)) + ((u64)v << t.K) + t.b0 + g;
+      u32 x[L];
+#pragma unroll
+      for (int j = 0; j < L; j++) x[j] = a.in[(u64)j * n + src];
       if constexpr (MUL) {
-        u32 x[L], y[L], r[L];
+        u32 y[L], r[L];
 #pragma unroll
-        for (int j = 0; j < L; j++) {
-          x[j] = a.in[(u64)j * n + src];
-          y[j] = a.in2[(u64)j * n + src];
-        }
+        for (int j = 0; j < L; j++) y[j] = a.in2[(u64)j * n + src];
         pointwise_digits<L, FW>(r, x, y, c);
-#pragma unroll
-        for (int j = 0; j < L; j++) lds[(j * t.rows + u) * t.C + g] = r[j];
+        lds_put<L>(lds, t.E, u * t.C + g, r);
       } else {
-#pragma unroll
-        for (int j = 0; j < L; j++) lds[(j * t.rows + u) * t.C + g] = a.in[(u64)j * n + src];
+        lds_put<L>(lds, t.E, u * t.C + g, x);
       }
     }
   }
@@ -612,7 +602,6 @@ __device__ __forceinline__ void pass_tile(u32* lds, const NttPassArgs& a, const 
 
   // ---- store (canonical residues on the last pass), 4 words per lane per limb
   const u32 logn = a.logn;
-  auto finish = [&](u32* x) { finish_elem<L, FW>(x, a, c); };
   // 4 elements of L limbs (and the scale multiply) stay in registers
   // (up to 10 limbs: at 11 to 16 limbs the 4L live words cost occupancy, and
   // 2^16-point transforms measured 3 to 10% slower)
@@ -626,15 +615,8 @@ __device__ __forceinline__ void pass_tile(u32* lds, const NttPassArgs& a, const 
       u64 dst = (t.ro << (t.K + t.k)) + ((u64)v << t.K) + t.b0 + g;
       u32 x[4][L];
 #pragma unroll
-      for (int j = 0; j < L; j++) {
-        uint4 w = *reinterpret_cast<const uint4*>(lds + (j * t.rows + u) * t.C + g);
-        x[0][j] = w.x;
-        x[1][j] = w.y;
-        x[2][j] = w.z;
-        x[3][j] = w.w;
-      }
-#pragma unroll
-      for (int q4 = 0; q4 < 4; q4++) finish(x[q4]);
+      for (int q4 = 0; q4 < 4; q4++) lds_get<L>(x[q4], lds, t.E, u * t.C + g + q4);
+      finish_elems<L, FW, 4>(x, a, c);
 #pragma unroll
       for (int j = 0; j < L; j++)
         *reinterpret_cast<uint4*>(a.out + (u64)j * n + dst) = make_uint4(x[0][j], x[1][j], x[2][j], x[3][j]);
@@ -647,12 +629,8 @@ __device__ __forceinline__ void pass_tile(u32* lds, const NttPassArgs& a, const 
       u64 dst = ((u64)rev_bits((u32)(t.o0 + g), logn - t.k) << t.k) + v;
       u32 x[4][L];
 #pragma unroll
-      for (int q4 = 0; q4 < 4; q4++) {
-        u32 u = rev_bits(v + q4, t.k);
-#pragma unroll
-        for (int j = 0; j < L; j++) x[q4][j] = lds[(j * t.rows + u) * t.C + g];
-        finish(x[q4]);
-      }
+      for (int q4 = 0; q4 < 4; q4++) lds_get<L>(x[q4], lds, t.E, rev_bits(v + q4, t.k) * t.C + g);
+      finish_elems<L, FW, 4>(x, a, c);
 #pragma unroll
       for (int j = 0; j < L; j++)
         *reinterpret_cast<uint4*>(a.out + (u64)j * n + dst) = make_uint4(x[0][j], x[1][j], x[2][j], x[3][j]);
@@ -673,9 +651,8 @@ __device__ __forceinline__ void pass_tile(u32* lds, const NttPassArgs& a, const 
         dst = (t.ro << (t.K + t.k)) + ((u64)v << t.K) + t.b0 + g;
       }
       u32 x[L];
-#pragma unroll
-      for (int j = 0; j < L; j++) x[j] = lds[(j * t.rows + u) * t.C + g];
-      finish(x);
+      lds_get<L>(x, lds, t.E, u * t.C + g);
+      finish_elems<L, FW, 1>(&x, a, c);
 #pragma unroll
       for (int j = 0; j < L; j++) a.out[(u64)j * n + dst] = x[j];
     }
@@ -688,13 +665,16 @@ template <int L, int R>
 struct PassTraits {
   static constexpr int live = L << R;
   static constexpr int max_threads = live <= 16 ? 1024 : (live <= 32 ? 512 : 256);
+  // radix-4 units of 7 or 8 limbs need just over the 128 registers that four
+  // waves per SIMD leave a lane
+  static constexpr int min_waves = R == 2 && live > 24 && live <= 32 ? 4 : 1;
 };
 
 // One pass of one transform: workgroup b runs tile b.
 template <int L, int R, bool MUL, bool LASTX, int AR = kArithLazy>
-__global__ __launch_bounds__((PassTraits<L, R>::max_threads)) void ntt_pass_kernel(NttPassArgs a,
+__global__ __launch_bounds__((PassTraits<L, R>::max_threads), (PassTraits<L, R>::min_waves)) void ntt_pass_kernel(NttPassArgs a,
                                                                                  NttC<L, AR == kArithFull> c) {
-  extern __shared__ u32 lds[];
+  extern __shared__ __align__(16) u32 lds[];
   pass_tile<L, R, MUL, LASTX, AR>(lds, a, c, blockIdx.x);
 }
 
@@ -717,10 +697,10 @@ inline bool fused_last_applies(const NttPassArgs& a, uint32_t threads, uint32_t 
 // Workgroup i runs item i; items are sorted by decreasing cost, so the
 // dispatcher hands out the largest tiles first.
 template <int L, int R, bool MUL, bool LASTX, bool FW = false>
-__global__ __launch_bounds__((PassTraits<L, R>::max_threads)) void ntt_batch_kernel(
+__global__ __launch_bounds__((PassTraits<L, R>::max_threads), (PassTraits<L, R>::min_waves)) void ntt_batch_kernel(
     const NttPassArgs* __restrict__ passes, const NttC<L, FW>* __restrict__ consts, const uint2* __restrict__ items,
     u32 nitems) {
-  extern __shared__ u32 lds[];
+  extern __shared__ __align__(16) u32 lds[];
   const u32 i = blockIdx.x;
   if (i >= nitems) return;
   const uint2 it = items[i];
@@ -734,7 +714,7 @@ __global__ __launch_bounds__((PassTraits<L, R>::max_threads)) void ntt_batch_ker
   pass_tile<L, R, MUL, LASTX, FW ? kArithFull : kArithLazy>(lds, a, c, it.y);
 }
 
-// Twiddle table: entry e = 2^s + i' holds w^(i' * 2^(logn-s-1)) * 2^(32L) mod q.
+// Twiddle table: entry e = 2^s + i' holds w^(i' * 2^(logn-s-1)) mod q and its quotient.
 // ladder[b] = w^(2^b) * 2^(32L) mod q; the product of the ladder entries for the
 // set bits of the exponent stays in Montgomery form.
 // FW (full-width modulus): the products keep the carry out of the top limb.
@@ -765,25 +745,49 @@ __global__ __launch_bounds__(256) void twiddle_kernel(u32* __restrict__ tw, u64 
       }
     }
   }
-  // acc = w^x * 2^(32L); times 2^(bD) * 2^(-32L) gives the digit-form Montgomery value
-  constexpr int S = digit_stride(L, FW);
-  u32 ad[L], wm[L], d[S];
+  // acc = w^x 2^(32L).  Times 1 it gives w^x itself; times adj = 2^(bD) it
+  // gives r = w^x R mod q (R = 2^(bD)), whose Montgomery digits
+  // m = -r q^-1 mod R are floor(w^x R / q), since w^x R - r is that times q.
+  constexpr int b = Digits<L, FW>::b, D = Digits<L, FW>::D, S = tw_words(L, FW);
+  u32 ad[L], one[L], wm[L], wp[L], r[D], d[S];
 #pragma unroll
-  for (int j = 0; j < L; j++) ad[j] = adj[j];
-  if constexpr (FW)
+  for (int j = 0; j < L; j++) {
+    ad[j] = adj[j];
+    one[j] = j == 0 ? 1u : 0u;
+  }
+  if constexpr (FW) {
     mont_mul_fw<L>(wm, acc, ad, c.q, c.qinv, c.q);
-  else
+    mont_mul_fw<L>(wp, acc, one, c.q, c.qinv, c.q);
+  } else {
     mont_mul<L>(wm, acc, ad, c.q, c.qinv);
-  to_digits<L, FW>(d, wm);
-  if (S > Digits<L, FW>::D) d[S - 1] = 0;
+    mont_mul<L>(wp, acc, one, c.q, c.qinv);
+  }
+  to_digits<L, FW>(r, wm);
+  u64 carry = 0;
 #pragma unroll
-  for (int j = 0; j < S; j++) tw[e * S + j] = d[j];
+  for (int i = 0; i < D; i++) {
+    carry += r[i];
+#pragma unroll
+    for (int j = 0; j < i; j++) carry += (u64)d[j] * c.qd[i - j];
+    d[i] = ((u32)carry * c.qinvd) & Digits<L, FW>::mask;
+    carry += (u64)d[i] * c.qd[0];
+    carry >>= b;
+  }
+  to_digits<L, FW>(d + D, wp);
+#pragma unroll
+  for (int j = 2 * D; j < S; j++) d[j] = 0;
+  uint4* out = reinterpret_cast<uint4*>(tw);
+#pragma unroll
+  for (int j = 0; j < S / 4; j++) out[j * n + e] = make_uint4(d[4 * j], d[4 * j + 1], d[4 * j + 2], d[4 * j + 3]);
 }
 
 template <int L, bool FW = false>
-inline NttC<L, FW> make_consts(const FieldRaw& f, const DigitConsts& dc, const NttConsts* nc) {
+inline NttC<L, FW> make_consts(const FieldRaw& f, const DigitConsts& dc) {
   NttC<L, FW> c;
-  for (int j = 0; j < Digits<L, FW>::D; j++) c.qd[j] = dc.qd[j];
+  for (int j = 0; j < Digits<L, FW>::D; j++) {
+    c.qd[j] = dc.qd[j];
+    c.nqd[j] = dc.nqd[j];
+  }
   c.qinvd = dc.qinvd;
   u64 carry = 0;
   for (int j = 0; j < L; j++) {
@@ -792,7 +796,6 @@ inline NttC<L, FW> make_consts(const FieldRaw& f, const DigitConsts& dc, const N
     c.q2[j] = (u32)d;
     carry = d >> 32;
   }
-  for (int j = 0; j < Digits<L, FW>::D; j++) c.nscaled[j] = nc ? nc->nscale_d[j] : 0;
   c.qinv = f.qinv;
   return c;
 }
@@ -859,9 +862,9 @@ int launch_pass_LR(const NttC<L>& c, const NttPassArgs& a, uint32_t threads, uin
 
 // full-width modulus: radix-2 and radix-4 units, no cross-lane variant
 template <int L>
-int launch_pass_fw(const FieldRaw& f, const DigitConsts& dc, const NttPassArgs& a, const NttConsts& nc,
-                   uint32_t threads, uint64_t tiles, uint32_t radix_log, hipStream_t s) {
-  NttC<L, true> c = make_consts<L, true>(f, dc, &nc);
+int launch_pass_fw(const FieldRaw& f, const DigitConsts& dc, const NttPassArgs& a, uint32_t threads,
+                   uint64_t tiles, uint32_t radix_log, hipStream_t s) {
+  NttC<L, true> c = make_consts<L, true>(f, dc);
   if (radix_log == 1)
     return a.in2 ? launch_pass_LRM<L, 1, true, false, kArithFull>(c, a, threads, tiles, s)
                  : launch_pass_LRM<L, 1, false, false, kArithFull>(c, a, threads, tiles, s);
@@ -874,11 +877,11 @@ int launch_pass_fw(const FieldRaw& f, const DigitConsts& dc, const NttPassArgs& 
 }
 
 template <int L>
-int launch_pass_L(const FieldRaw& f, const DigitConsts& dc, const NttPassArgs& a, const NttConsts& nc,
-                  uint32_t threads, uint64_t tiles, uint32_t radix_log, uint32_t kara, hipStream_t s) {
+int launch_pass_L(const FieldRaw& f, const DigitConsts& dc, const NttPassArgs& a, uint32_t threads,
+                  uint64_t tiles, uint32_t radix_log, uint32_t kara, hipStream_t s) {
   if (f.fw)
-    return kara ? (int)hipErrorInvalidValue : launch_pass_fw<L>(f, dc, a, nc, threads, tiles, radix_log, s);
-  NttC<L> c = make_consts<L>(f, dc, &nc);
+    return kara ? (int)hipErrorInvalidValue : launch_pass_fw<L>(f, dc, a, threads, tiles, radix_log, s);
+  NttC<L> c = make_consts<L>(f, dc);
   if (kara) {
     // the Karatsuba butterfly: radix-2 units, 2 to 24 limbs, no cross-lane variant
     if constexpr (L >= 2 && L <= kMaxLimbsKara) {
@@ -1006,11 +1009,11 @@ int launch_tw_L(const FieldRaw& f, const DigitConsts& dc, uint32_t* tw, uint64_t
   const u32* adj = one_m + L;
   u64 blocks = (n + 255) / 256;
   if (f.fw) {
-    NttC<L, true> c = make_consts<L, true>(f, dc, nullptr);
+    NttC<L, true> c = make_consts<L, true>(f, dc);
     hipLaunchKernelGGL((twiddle_kernel<L, true>), dim3((unsigned)blocks), dim3(256), 0, s, tw, n, logn, d_ladder, c,
                        one_m, adj);
   } else {
-    NttC<L> c = make_consts<L>(f, dc, nullptr);
+    NttC<L> c = make_consts<L>(f, dc);
     hipLaunchKernelGGL((twiddle_kernel<L>), dim3((unsigned)blocks), dim3(256), 0, s, tw, n, logn, d_ladder, c,
                        one_m, adj);
   }
@@ -1019,7 +1022,7 @@ int launch_tw_L(const FieldRaw& f, const DigitConsts& dc, uint32_t* tw, uint64_t
 
 // the per-limb-count entry points, instantiated once (in ntt_inst_*.hip)
 #define MOMA_NTT_DECLARE(PREFIX, LL)                                                                              \
-  PREFIX template int launch_pass_L<LL>(const FieldRaw&, const DigitConsts&, const NttPassArgs&, const NttConsts&, \
+  PREFIX template int launch_pass_L<LL>(const FieldRaw&, const DigitConsts&, const NttPassArgs&,                   \
                                         uint32_t, uint64_t, uint32_t, uint32_t, hipStream_t);                       \
   PREFIX template int launch_batch_L<LL>(uint32_t, bool, bool, bool, uint32_t, size_t, uint32_t,                  \
                                          const NttPassArgs*, const void*, const uint2*, uint32_t, hipStream_t);     \

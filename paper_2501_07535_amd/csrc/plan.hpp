@@ -24,7 +24,7 @@ struct FieldEntry {
 };
 
 struct DirTables {
-  uint32_t* tw = nullptr;      // n entries x digit_stride(L) words, digit Montgomery form
+  uint32_t* tw = nullptr;      // n entries x tw_words(L) words: quotient and twiddle digits
   uint32_t* ladder = nullptr;  // (logn + 2) x L words: w^(2^b) in Montgomery form, then 1, then 2^(bD) mod q
 };
 
@@ -34,8 +34,9 @@ struct NttPlan {
   uint64_t n = 0;
   uint32_t logn = 0;
   DirTables fwd, inv;
-  NttConsts inv_consts;
-  NttConsts mul_consts;           // inverse after a fused pointwise product
+  uint32_t* scales = nullptr;     // the inverse's last-pass factor (2 D digits), then the one after a pointwise product
+  const uint32_t* inv_scale() const { return scales; }
+  const uint32_t* mul_scale() const { return scales + 2 * digit_count(fe->f.L, fe->f.fw); }
   uint32_t* scratch = nullptr;    // for in-place multi-pass calls
   uint32_t* spectra = nullptr;    // 2 x n x L words: the two forward transforms of a cyclic product
   NttSchedule sched;
@@ -46,6 +47,7 @@ struct NttPlan {
     (void)hipFree(fwd.ladder);
     (void)hipFree(inv.tw);
     (void)hipFree(inv.ladder);
+    (void)hipFree(scales);
     (void)hipFree(scratch);
     (void)hipFree(spectra);
   }

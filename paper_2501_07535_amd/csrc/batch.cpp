@@ -150,7 +150,10 @@ static int batch_create(const moma_ntt_job_t* jobs, uint32_t njobs, BatchImpl& b
       uint64_t cost = E * ps.k;
       uint32_t ph = phase0 + (uint32_t)i;
       auto& v = g.items[ph];
-      for (uint64_t tl = 0; tl < ps.tiles; tl++) v.push_back({cost, make_uint2(rec, (uint32_t)tl)});
+      // (workgroup order, as in a lone call: the items of one record stay
+      // together in the sort, so tiles 8 apart here run on one XCD)
+      const uint32_t xg = xcd_group_log(ps.logc, ps.tiles);
+      for (uint64_t tl = 0; tl < ps.tiles; tl++) v.push_back({cost, make_uint2(rec, xcd_tile((uint32_t)tl, xg))});
       size_t bytes = (size_t)E * f.L * sizeof(uint32_t);
       g.lds[ph] = std::max(g.lds[ph], bytes);
     }

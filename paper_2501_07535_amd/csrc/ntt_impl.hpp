@@ -670,12 +670,12 @@ struct PassTraits {
   static constexpr int min_waves = R == 2 && live > 24 && live <= 32 ? 4 : 1;
 };
 
-// One pass of one transform: workgroup b runs tile b.
+// One pass of one transform: one tile per workgroup.
 template <int L, int R, bool MUL, bool LASTX, int AR = kArithLazy>
 __global__ __launch_bounds__((PassTraits<L, R>::max_threads), (PassTraits<L, R>::min_waves)) void ntt_pass_kernel(NttPassArgs a,
                                                                                  NttC<L, AR == kArithFull> c) {
   extern __shared__ __align__(16) u32 lds[];
-  pass_tile<L, R, MUL, LASTX, AR>(lds, a, c, blockIdx.x);
+  pass_tile<L, R, MUL, LASTX, AR>(lds, a, c, a.xcd_log ? xcd_tile(blockIdx.x, a.xcd_log) : blockIdx.x);
 }
 
 // Whether a pass with radix-4 units ends with ntt_round_last: its stage count
@@ -801,8 +801,10 @@ inline NttC<L, FW> make_consts(const FieldRaw& f, const DigitConsts& dc) {
 }
 
 template <int L, int R, bool MUL, bool LASTX, int AR = kArithLazy>
-int launch_pass_LRM(const NttC<L, AR == kArithFull>& c, const NttPassArgs& a, uint32_t threads, uint64_t tiles,
+int launch_pass_LRM(const NttC<L, AR == kArithFull>& c, const NttPassArgs& pass, uint32_t threads, uint64_t tiles,
                     hipStream_t s) {
+  NttPassArgs a = pass;
+  a.xcd_log = xcd_group_log(a.logc, tiles);
   size_t lds = (size_t)L * ((size_t)1 << (a.k + a.logc)) * sizeof(u32);
   static std::atomic<bool> attr_set{false};  // several host threads may launch at once
   if (lds > 65536 && !attr_set.load(std::memory_order_acquire)) {

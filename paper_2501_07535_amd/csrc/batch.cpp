@@ -191,13 +191,13 @@ static int batch_create(const moma_ntt_job_t* jobs, uint32_t njobs, BatchImpl& b
       a.ls = (uint32_t)fe->f.Ls;
       if (op == OP_VMUL && !fe->f.fw) a.variant = vmul_variant(fe->f.L);
       if (op == OP_AXPY) {
-        rc = axpy_alpha(*fe, job.alpha, job.limbs, a.alpha_m);
+        rc = axpy_alpha(*fe, job.alpha, job.limbs, &a);
         if (rc) return set_error(rc, tag + g_detail);
       }
       BGroup& g = bgroups[std::make_tuple(op, fe->f.L, a.variant, fe->f.fw != 0)];
       const uint32_t rec = (uint32_t)g.recs.size();
       g.recs.push_back({job.d_in, job.d_in2, job.d_out, job.n});
-      size_t cb = blas_consts_bytes(fe->f.L), off = g.consts.size();
+      size_t cb = blas_consts_bytes(fe->f.L, fe->f.fw != 0), off = g.consts.size();
       g.consts.resize(off + cb);
       blas_fill_consts(fe->f, a, g.consts.data() + off);
       const uint64_t blocks = (job.n + 255) / 256;

@@ -12,20 +12,29 @@
 
 namespace moma {
 
-template <int L>
+template <int L, bool FW>
 struct BlasC {
   u32 q[L];
-  u32 qinv;
-  BarrettC<L> bc;
-  u32 alpha_m[L];
-  u32 r2[L];  // 2^(64L) mod q (full-width vmul)
+  u32 nqd[Digits<L, FW>::D];
+  u32 alpha_d[Digits<L, FW>::D];
+  u32 alpha_q[Digits<L, FW>::D];
+  BarrettC<L, FW> bc;
+  BarrettKaraC<L> kc;
 };
 
-// One element's operation.  A full-width modulus (FW: no headroom for Barrett's
-// pre-scaled modulus) multiplies by Montgomery products that keep the carry
-// out of the top limb: vmul = mont(mont(a, b), 2^(64L) mod q).
+// One element's operation.  A full-width modulus (FW) differs only where a sum
+// or a product below 2q can carry out of the top limb.
 template <int L, int OP, bool KARA, bool FW>
-__device__ __forceinline__ void blas_elem(u32* r, const u32* a, const u32* b, const BlasC<L>& c) {
+__device__ __forceinline__ void blas_elem(u32* r, const u32* a, const u32* b, const BlasC<L, FW>& c) {
+  if constexpr (OP == OP_VMUL) {
+    if constexpr (KARA)
+      barrett_mul_kara<L>(r, a, b, c.kc);
+    else
+      barrett_mul_digits<L, FW>(r, a, b, c.bc);
+    return;
+  }
+  u32 t[L], x[L], top = 0;
+  if constexpr (OP == OP_AXPY) quot_mul<L, FW>(t, a, c.alpha_d, c.alpha_q, c.nqd, &top);  // alpha x in [0, 2q)
   if constexpr (FW) {
     u32 qv[L];
     to_vgprs<L>(qv, c.q);
@@ -33,28 +42,18 @@ __device__ __forceinline__ void blas_elem(u32* r, const u32* a, const u32* b, co
       mod_add_fw<L>(r, a, b, qv);
     } else if constexpr (OP == OP_VSUB) {
       mod_sub_v<L>(r, a, b, qv);
-    } else if constexpr (OP == OP_VMUL) {
-      u32 t[L], r2v[L];
-      mont_mul_fw<L>(t, a, b, c.q, c.qinv, qv);    // a b 2^(-32L)
-      to_vgprs<L>(r2v, c.r2);
-      mont_mul_fw<L>(r, t, r2v, c.q, c.qinv, qv);  // times 2^(64L) 2^(-32L)
     } else {
-      u32 t[L], av[L];
-      to_vgprs<L>(av, c.alpha_m);
-      mont_mul_fw<L>(t, a, av, c.q, c.qinv, qv);   // alpha * x
-      mod_add_fw<L>(r, t, b, qv);                  // + y
+      reduce_top<L>(x, t, top, qv);
+      mod_add_fw<L>(r, x, b, qv);
     }
   } else {
     if constexpr (OP == OP_VADD) {
       mod_add<L>(r, a, b, c.q);
     } else if constexpr (OP == OP_VSUB) {
       mod_sub<L>(r, a, b, c.q);
-    } else if constexpr (OP == OP_VMUL) {
-      barrett_mul<L, KARA>(r, a, b, c.bc);
     } else {
-      u32 t[L];
-      mont_mul<L>(t, a, c.alpha_m, c.q, c.qinv);  // alpha * x
-      mod_add<L>(r, t, b, c.q);                   // + y
+      reduce_once<L>(x, t, c.q);
+      mod_add<L>(r, x, b, c.q);
     }
   }
 }
@@ -65,7 +64,7 @@ __device__ __forceinline__ void blas_elem(u32* r, const u32* a, const u32* b, co
 // against 280 us with one element per lane.
 template <int L, int OP, bool KARA, bool FW>
 __global__ __launch_bounds__(256) void blas_kernel(const u32* __restrict__ pa, const u32* __restrict__ pb,
-                                                   u32* __restrict__ pout, u64 n, BlasC<L> c) {
+                                                   u32* __restrict__ pout, u64 n, BlasC<L, FW> c) {
   const u64 i = (u64)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
   u32 a[L], b[L], r[L];
@@ -80,7 +79,7 @@ __global__ __launch_bounds__(256) void blas_kernel(const u32* __restrict__ pa, c
 }
 
 template <int L, int OP, bool KARA, bool FW>
-static int launch_blas_LK(const BlasArgs& a, const BlasC<L>& c, hipStream_t s) {
+static int launch_blas_LK(const BlasArgs& a, const BlasC<L, FW>& c, hipStream_t s) {
   const unsigned T = 256;
   const u64 blocks = (a.n + T - 1) / T;
   hipLaunchKernelGGL((blas_kernel<L, OP, KARA, FW>), dim3((unsigned)blocks), dim3(T), 0, s, a.a, a.b, a.out, a.n,
@@ -88,28 +87,34 @@ static int launch_blas_LK(const BlasArgs& a, const BlasC<L>& c, hipStream_t s) {
   return (int)hipGetLastError();
 }
 
-template <int L>
-static BlasC<L> blas_consts(const FieldRaw& f, const BlasArgs& a) {
-  BlasC<L> c;
+template <int L, bool FW>
+static BlasC<L, FW> blas_consts(const FieldRaw& f, const BlasArgs& a) {
+  BlasC<L, FW> c;
   memset(&c, 0, sizeof(c));
   for (int j = 0; j < L; j++) {
     c.q[j] = f.q[j];
-    c.bc.qn[j] = f.qn[j];
-    c.bc.mu[j] = f.mu[j];
-    c.alpha_m[j] = a.alpha_m[j];
-    c.r2[j] = f.r2[j];
+    c.bc.qs[j] = f.vd && j ? f.q[j] << f.vd | f.q[j - 1] >> (32 - f.vd) : f.q[j] << f.vd;
+    c.kc.qn[j] = f.qn[j];
+    c.kc.mu[j] = f.mu[j];
   }
-  c.qinv = f.qinv;
-  c.bc.d = f.d;
+  for (int j = 0; j < Digits<L, FW>::D; j++) {
+    c.nqd[j] = f.nqd[j];
+    c.alpha_d[j] = a.alpha_d[j];
+    c.alpha_q[j] = a.alpha_q[j];
+    c.bc.mu[j] = f.vmu[j];
+    c.bc.nqn[j] = f.vnqn[j];
+  }
+  c.bc.d = f.vd;
+  c.kc.d = f.d;
   return c;
 }
 
-// A full-width modulus runs the Montgomery products (the product variant is a
-// choice of Barrett's products and does not apply).
+// (The product variant is a choice for moduli with headroom: the Karatsuba form
+// needs it, and a full-width modulus always runs the digit form.)
 template <int L, int OP>
 static int launch_blas_L(const FieldRaw& f, const BlasArgs& a, hipStream_t s) {
-  BlasC<L> c = blas_consts<L>(f, a);
-  if (f.fw) return launch_blas_LK<L, OP, false, true>(a, c, s);
+  if (f.fw) return launch_blas_LK<L, OP, false, true>(a, blas_consts<L, true>(f, a), s);
+  const BlasC<L, false> c = blas_consts<L, false>(f, a);
   if constexpr (OP == OP_VMUL && L >= 2) {
     if (a.variant == 1) return launch_blas_LK<L, OP, true, false>(a, c, s);
   }
@@ -147,7 +152,7 @@ int launch_blas(int op, const FieldRaw& f, const BlasArgs& a, hipStream_t s) {
 
 template <int L, int OP, bool KARA, bool FW>
 __global__ __launch_bounds__(256) void blas_batch_kernel(const BlasJobRec* __restrict__ recs,
-                                                         const BlasC<L>* __restrict__ consts,
+                                                         const BlasC<L, FW>* __restrict__ consts,
                                                          const uint2* __restrict__ items, u32 nitems) {
   const u32 w = blockIdx.x;
   if (w >= nitems) return;
@@ -157,7 +162,7 @@ __global__ __launch_bounds__(256) void blas_batch_kernel(const BlasJobRec* __res
   r.a = load_global_ptr(&rec->a);
   r.b = load_global_ptr(&rec->b);
   r.out = load_global_ptr(&rec->out);
-  const BlasC<L> c = consts[it.x];
+  const BlasC<L, FW> c = consts[it.x];
   const u64 i = (u64)it.y * blockDim.x + threadIdx.x;
   if (i >= r.n) return;
   const u64 n = r.n;
@@ -172,10 +177,10 @@ __global__ __launch_bounds__(256) void blas_batch_kernel(const BlasJobRec* __res
   for (int j = 0; j < L; j++) r.out[(u64)j * n + i] = res[j];
 }
 
-size_t blas_consts_bytes(int L) {
+size_t blas_consts_bytes(int L, bool fw) {
   switch (L) {
 #define CASE(LL) \
-  case LL: return sizeof(BlasC<LL>);
+  case LL: return fw ? sizeof(BlasC<LL, true>) : sizeof(BlasC<LL, false>);
     MOMA_FOR_EACH_L(CASE)
 #undef CASE
   }
@@ -184,12 +189,16 @@ size_t blas_consts_bytes(int L) {
 
 void blas_fill_consts(const FieldRaw& f, const BlasArgs& a, void* dst) {
   switch (f.L) {
-#define CASE(LL)                                  \
-  case LL: {                                      \
-    BlasC<LL> c = blas_consts<LL>(f, a);          \
-    memcpy(dst, &c, sizeof(c));                   \
-    return;                                       \
-  }
+#define CASE(LL)                                                     \
+  case LL:                                                           \
+    if (f.fw) {                                                      \
+      const BlasC<LL, true> c = blas_consts<LL, true>(f, a);         \
+      memcpy(dst, &c, sizeof(c));                                    \
+    } else {                                                         \
+      const BlasC<LL, false> c = blas_consts<LL, false>(f, a);       \
+      memcpy(dst, &c, sizeof(c));                                    \
+    }                                                                \
+    return;
     MOMA_FOR_EACH_L(CASE)
 #undef CASE
   }
@@ -199,7 +208,7 @@ template <int L, int OP, bool KARA, bool FW = false>
 static int launch_blas_batch_LOK(const void* recs, const void* consts, const uint2* items, uint32_t nitems,
                                  hipStream_t s) {
   hipLaunchKernelGGL((blas_batch_kernel<L, OP, KARA, FW>), dim3(nitems), dim3(256), 0, s, (const BlasJobRec*)recs,
-                     (const BlasC<L>*)consts, items, nitems);
+                     (const BlasC<L, FW>*)consts, items, nitems);
   return (int)hipGetLastError();
 }
 

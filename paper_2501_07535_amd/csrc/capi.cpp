@@ -81,7 +81,6 @@ int build_field(const uint32_t* q, uint32_t limbs, std::shared_ptr<FieldEntry>* 
   f.qinv = neg_inv32(f.q[0]);
   HBig one_m = HBig::mod(HBig::pow2(32 * f.L), Q);
   one_m.to_limbs(f.one_m, kMaxLimbs);
-  HBig::mod(HBig::pow2(64 * f.L), Q).to_limbs(f.r2, kMaxLimbs);
   if (!f.fw) {
     int Mn = 32 * f.L - 4;
     f.d = (uint32_t)(Mn - M);
@@ -98,7 +97,16 @@ int build_field(const uint32_t* q, uint32_t limbs, std::shared_ptr<FieldEntry>* 
     memset(&dc, 0, sizeof(dc));
     int b = digit_bits(f.L), D = digit_count(f.L, f.fw);
     digits_of(Q, f.L, f.fw, dc.qd);
-    digits_of(HBig::sub(HBig::pow2(b * D), Q), f.L, f.fw, dc.nqd);
+    digits_of(HBig::sub(HBig::pow2(b * D), Q), f.L, f.fw, f.nqd);
+    // vmul: the modulus scaled to bD - 1 bits
+    f.vd = (uint32_t)((f.fw ? 32 * f.L : 32 * f.L - 4) - M);
+    HBig qs = HBig::shl(Q, (int)f.vd + barrett_off(f.L, f.fw)), vmu;
+    digits_of(HBig::sub(HBig::pow2(b * D), qs), f.L, f.fw, f.vnqn);
+    HBig::divmod(HBig::pow2(2 * b * D), qs, &vmu, nullptr);
+    digits_of(vmu, f.L, f.fw, f.vmu);
+    uint32_t vtop[2] = {0, 0};
+    HBig::shr(vmu, b * (D - 1)).to_limbs(vtop, 2);
+    f.vmu[D - 1] = vtop[0];
     dc.qinvd = f.qinv & ((1u << b) - 1);
     fe->adj = HBig::mod(HBig::pow2(b * D), Q);
     fe->adj.to_limbs(dc.adj, kMaxLimbs);
@@ -577,19 +585,20 @@ uint32_t vmul_variant(int L) {
   return g_vmul_variant[L];
 }
 
-int axpy_alpha(FieldEntry& fe, const uint32_t* alpha, uint32_t limbs, uint32_t* alpha_m) {
+int axpy_alpha(FieldEntry& fe, const uint32_t* alpha, uint32_t limbs, BlasArgs* a) {
   if (!alpha) return set_error(MOMA_E_ARG, "alpha is NULL");
   std::vector<uint32_t> key(alpha, alpha + limbs);
   std::lock_guard<std::mutex> lk(g_mu);
   if (fe.alpha_key != key) {
-    HBig A = HBig::from_limbs(alpha, (int)limbs);
+    HBig A = HBig::from_limbs(alpha, (int)limbs), aq;
     if (HBig::cmp(A, fe.Q) >= 0) return set_error(MOMA_E_ARG, "alpha must be < q");
-    HBig am = HBig::mulmod(A, fe.one_m, fe.Q);
-    fe.alpha_m.assign(kMaxLimbs, 0);
-    am.to_limbs(fe.alpha_m.data(), kMaxLimbs);
+    HBig::divmod(HBig::shl(A, digit_bits(fe.f.L) * digit_count(fe.f.L, fe.f.fw)), fe.Q, &aq, nullptr);
+    digits_of(A, fe.f.L, fe.f.fw, fe.alpha_d);
+    digits_of(aq, fe.f.L, fe.f.fw, fe.alpha_q);
     fe.alpha_key = key;
   }
-  memcpy(alpha_m, fe.alpha_m.data(), sizeof(uint32_t) * kMaxLimbs);
+  memcpy(a->alpha_d, fe.alpha_d, sizeof(fe.alpha_d));
+  memcpy(a->alpha_q, fe.alpha_q, sizeof(fe.alpha_q));
   return MOMA_OK;
 }
 
@@ -610,7 +619,7 @@ static int blas_entry(int op, const uint32_t* q, uint32_t limbs, uint64_t n, con
   a.ls = (uint32_t)fe->f.Ls;
   if (op == OP_VMUL) a.variant = vmul_variant(fe->f.L);
   if (op == OP_AXPY) {
-    int r = axpy_alpha(*fe, alpha, limbs, a.alpha_m);
+    int r = axpy_alpha(*fe, alpha, limbs, &a);
     if (r) return r;
   }
   hipStream_t s = (hipStream_t)stream;

@@ -20,6 +20,11 @@ constexpr int digit_bits(int L) { return L <= 28 ? 29 : 28; }
 constexpr int digit_count(int L, bool fw = false) {
   return (32 * L - (fw ? 0 : 1) + digit_bits(L) - 1) / digit_bits(L);
 }
+// fixed scaling of vmul's first operand (bits): q 2^(W0 - bitlen(q)) has W0 bits
+// (32L, full width, or 32L - 4), and scaled once more by this it has bD - 1
+constexpr int barrett_off(int L, bool fw = false) {
+  return digit_bits(L) * digit_count(L, fw) - 1 - (fw ? 32 * L : 32 * L - 4);
+}
 // words of one twiddle table entry: the quotient's digits, the twiddle's
 // digits, padded to whole 16-byte loads
 constexpr int tw_words(int L, bool fw = false) { return (2 * digit_count(L, fw) + 3) / 4 * 4; }
@@ -49,7 +54,10 @@ struct FieldRaw {
   uint32_t qn[kMaxLimbs];  // q * 2^d, bitlen 32L - 4 (Barrett)
   uint32_t mu[kMaxLimbs];  // floor(2^(2(32L-4)+3) / qn)
   uint32_t d;              // Barrett pre-scale shift
-  uint32_t r2[kMaxLimbs];  // 2^(64L) mod q: full-width vmul (two Montgomery products)
+  uint32_t vd;             // vmul in digits: bits that q lacks to W0 (barrett_off)
+  uint32_t vmu[40];        // and its quotient constant, the top digit with the bits above bD
+  uint32_t vnqn[40];       // 2^(bD) minus the scaled modulus, in digits
+  uint32_t nqd[40];        // 2^(bD) - q in digits
 };
 
 enum BlasOp { OP_VADD = 0, OP_VSUB = 1, OP_VMUL = 2, OP_AXPY = 3 };
@@ -59,9 +67,10 @@ struct BlasArgs {
   const uint32_t* b;
   uint32_t* out;
   uint64_t n;
-  uint32_t alpha_m[kMaxLimbs];  // axpy: alpha * 2^(32L) mod q (Montgomery form)
-  uint32_t variant;              // vmul: 0 schoolbook products, 1 Karatsuba (L >= 2)
-  uint32_t ls;                   // storage planes (>= L; the planes above L are written as zero)
+  uint32_t alpha_d[40];  // axpy: alpha in digits
+  uint32_t alpha_q[40];  // and its quotient floor(alpha 2^(bD) / q)
+  uint32_t variant;      // vmul: 0 schoolbook products, 1 Karatsuba (L >= 2)
+  uint32_t ls;           // storage planes (>= L; the planes above L are written as zero)
 };
 
 // One pass of the transform: k radix-2 stages [K, K+k) over tiles of C groups.
@@ -121,7 +130,6 @@ enum NttArith { kArithLazy = 0, kArithFull = 1, kArithKara = 2 };
 // per-modulus constants of the digit-form multiplies
 struct DigitConsts {
   uint32_t qd[40];   // q in b-bit digits (digit_count(L, fw) of them)
-  uint32_t nqd[40];  // 2^(bD) - q in digits
   uint32_t qinvd;    // -q^{-1} mod 2^b
   uint32_t adj[kMaxLimbs];  // 2^(b*D) mod q, converts a table entry to digit Montgomery form
 };

@@ -274,14 +274,19 @@ struct Digits {
   static constexpr u32 mask = (1u << b) - 1;
 };
 
-// d = y in base 2^b (y < 2^(b*D))
-template <int L, bool FW = false>
+// d = y 2^OFF in base 2^b (below 2^(b*D))
+template <int L, bool FW = false, int OFF = 0>
 __device__ __forceinline__ void to_digits(u32* d, const u32* y) {
   constexpr int b = Digits<L, FW>::b, D = Digits<L, FW>::D;
 #pragma unroll
   for (int i = 0; i < D; i++) {
     constexpr u32 m = Digits<L, FW>::mask;
-    const int pos = b * i, l = pos / 32, s = pos % 32;
+    const int pos = b * i - OFF;  // y's bit at the digit's bit 0
+    if (pos < 0) {
+      d[i] = pos <= -b ? 0u : (y[0] << (-pos & 31)) & m;
+      continue;
+    }
+    const int l = pos / 32, s = pos % 32;
     u32 lo = l < L ? y[l] : 0u, hi = l + 1 < L ? y[l + 1] : 0u;
     u32 v = s ? __builtin_amdgcn_alignbit(hi, lo, s) : lo;
     d[i] = v & m;
@@ -381,9 +386,9 @@ __device__ __forceinline__ void quot_digits(u32* m, const u32* a, const u32* wq)
   m[D - 1] = (u32)acc;
 }
 
-// limbs of a value given as raw columns: raw[i]'s low b bits are digit i (the
-// bits above are ignored, except in the last digit)
-template <int L, bool FW = false>
+// limbs of floor(value / 2^OFF), the value given as raw columns: raw[i]'s low b
+// bits are digit i (the bits above are ignored, except in the last digit)
+template <int L, bool FW = false, int OFF = 0>
 __device__ __forceinline__ void raw_to_limbs(u32* t, const u32* raw, u32* top) {
   constexpr int b = Digits<L, FW>::b, D = Digits<L, FW>::D;
   u32 hi[D];  // the digit at the top of its word
@@ -392,14 +397,14 @@ __device__ __forceinline__ void raw_to_limbs(u32* t, const u32* raw, u32* top) {
 #pragma unroll
   for (int j = 0; j <= L; j++) {
     if (j == L && !FW) break;
-    const int pos = 32 * j, i = pos / b, s = pos % b;  // the limb's lowest bit: bit s of digit i
+    const int pos = 32 * j + OFF, i = pos / b, s = pos % b;  // the limb's lowest bit: bit s of digit i
     u32 v;
     if (i >= D) {
       v = 0;
     } else if (i == D - 1) {
       v = raw[i] >> s;
     } else {
-      // digit i from bit s up, then digit i + 1 (all of it where b - s + b < 32)
+      // digit i from bit s up, then digit i + 1, then i + 2 where those are less than 32 bits
       const int have = 2 * b - s;
       v = __builtin_amdgcn_alignbit(raw[i + 1], hi[i], 32 - b + s);
       if (have < 32 && i + 1 < D - 1) {
@@ -664,12 +669,102 @@ __device__ __forceinline__ void ct_fw_tail(u32* x, u32* y, const u32* t, u32 top
   mod_sub_v<L>(y, s, tr, qv);
 }
 
-// Barrett constants for r = a*b mod q, following Listings 1 and 4 generalised to
-// L limbs.  The modulus is pre-scaled to qn = q * 2^d with bitlen(qn) = M = 32L-4,
+// Barrett multiplication (Eq. (barrett), Listing 4 generalised) in digits.  The
+// first operand is scaled so that the modulus qn = q 2^(d + off) has exactly
+// N = bD - 1 bits: by d in 32-bit words (W0 - bitlen(q), below 32; 0 for the
+// classes' own moduli) and by a fixed `off` in the way its digits are cut, which
+// puts every shift of the reduction on a digit boundary.
+//   P = a 2^(d + off) b;  m = floor(floor(P / B^(D-1)) mu / B^(D+1)),
+//   mu = floor(B^(2D) / qn) (its top digit takes the bits above bD, below 2^31);
+//   P - m qn in [0, 2 qn): one correction, then both scalings undone.
+// P has all its D^2 digit products; mu's product is taken from its columns D-1
+// and up (those below weigh less than 2^-b D of m's unit) and the last one mod
+// B^D: 2D^2 + 2D products, one v_mad_u64_u32 each, where the same method on
+// 32-bit words took 2.5 L^2 products of two instructions.
+// Bound by the issue of those products from 12 limbs on (below, by memory):
+// 2^24 products at 768 bits took 1534 us in words, 1202 us so.
+// m is floor(P / qn) or one less: what P loses below B^(D-1) and mu below 1
+// takes off less than 2^(2-b) and 2^(W0 - bD) <= 1/2 of m's unit.
+template <int L, bool FW = false>
+struct BarrettC {
+  static constexpr int W0 = FW ? 32 * L : 32 * L - 4;
+  static constexpr int off = barrett_off(L, FW);
+  u32 mu[Digits<L, FW>::D];
+  u32 nqn[Digits<L, FW>::D];  // B^D - qn
+  u32 qs[L];                  // q 2^d
+  u32 d;
+};
+
+template <int L, bool FW = false>
+__device__ __forceinline__ void barrett_mul_digits(u32* r, const u32* a, const u32* b, const BarrettC<L, FW>& c) {
+  constexpr int bits = Digits<L, FW>::b, D = Digits<L, FW>::D, off = BarrettC<L, FW>::off;
+  constexpr u32 mask = Digits<L, FW>::mask;
+  u32 as[L];
+  if (c.d == 0) {
+#pragma unroll
+    for (int i = 0; i < L; i++) as[i] = a[i];
+  } else {
+    as[0] = a[0] << c.d;
+#pragma unroll
+    for (int i = 1; i < L; i++) as[i] = __builtin_amdgcn_alignbit(a[i], a[i - 1], 32 - c.d);
+  }
+  u32 p[2 * D], m[D], raw[D];
+  {
+    u32 x[D], y[D];
+    to_digits<L, FW, off>(x, as);
+    to_digits<L, FW>(y, b);
+    u64 acc = 0;
+#pragma unroll
+    for (int k = 0; k < 2 * D - 1; k++) {
+#pragma unroll
+      for (int j = (k < D ? 0 : k - D + 1); j <= (k < D ? k : D - 1); j++) acc += (u64)x[j] * y[k - j];
+      p[k] = (u32)acc & mask;
+      acc >>= bits;
+    }
+    p[2 * D - 1] = (u32)acc;
+  }
+  u64 acc = 0;
+#pragma unroll
+  for (int k = D - 1; k < 2 * D; k++) {
+#pragma unroll
+    for (int i = k - D + 1; i <= (k < D ? k : D); i++) acc += (u64)p[D - 1 + i] * c.mu[k - i];
+    if (k > D) m[k - D - 1] = (u32)acc & mask;
+    acc >>= bits;
+  }
+  m[D - 1] = (u32)acc;
+  acc = 0;
+#pragma unroll
+  for (int i = 0; i < D; i++) {
+    acc += p[i];
+#pragma unroll
+    for (int j = 0; j <= i; j++) acc += (u64)m[j] * c.nqn[i - j];
+    if (i == D - 1) asm("" : "+v"(acc));  // as in quot_mul
+    raw[i] = (u32)acc;
+    acc >>= bits;
+  }
+  raw[D - 1] &= mask;
+  u32 t[L], red[L], top;
+  raw_to_limbs<L, FW, off>(t, raw, &top);
+  if constexpr (FW)
+    reduce_top<L>(red, t, top, c.qs);
+  else
+    reduce_once<L>(red, t, c.qs);
+  if (c.d == 0) {
+#pragma unroll
+    for (int i = 0; i < L; i++) r[i] = red[i];
+  } else {
+#pragma unroll
+    for (int i = 0; i < L - 1; i++) r[i] = __builtin_amdgcn_alignbit(red[i + 1], red[i], c.d);
+    r[L - 1] = red[L - 1] >> c.d;
+  }
+}
+
+// Constants of the Karatsuba variant, on 32-bit words, following Listings 1 and
+// 4 generalised to L limbs.  The modulus is pre-scaled to qn = q * 2^d with bitlen(qn) = M = 32L-4,
 // so the paper's shifts by M-2 and M+5 fall at fixed limb/bit positions:
 // mu = floor(2^(2M+3) / qn) < 2^(M+4) = 2^(32L).
 template <int L>
-struct BarrettC {
+struct BarrettKaraC {
   u32 qn[L];
   u32 mu[L];
   u32 d;
@@ -747,10 +842,9 @@ __device__ __forceinline__ void kara_mul(u32* t, const u32* a, const u32* b) {
 //   a' = a*2^d, t = a'*b < qn^2, r1 = t >> (M-2), r2 = (r1*mu) >> (M+5),
 //   t - r2*qn in [0, 2qn) (one correction), result = (that mod qn) >> d.
 // The subtraction uses only the low L limbs, as in _dmulmod: the difference
-// fits in L limbs.  Products: L^2 (a*b) + L^2 (r1*mu) + L(L+1)/2 (r2*qn).
-// KARA: the two full products by one level of Karatsuba (kara_mul).
-template <int L, bool KARA = false>
-__device__ __forceinline__ void barrett_mul(u32* r, const u32* a, const u32* b, const BarrettC<L>& c) {
+// fits in L limbs.  The two full products (a*b, r1*mu) by one level of Karatsuba.
+template <int L>
+__device__ __forceinline__ void barrett_mul_kara(u32* r, const u32* a, const u32* b, const BarrettKaraC<L>& c) {
   // a' = a << d (a < q so a' < qn < 2^(32L-4): no overflow past L limbs)
   u32 as[L];
   if (c.d == 0) {
@@ -763,42 +857,16 @@ __device__ __forceinline__ void barrett_mul(u32* r, const u32* a, const u32* b, 
   }
   // t = a' * b, 2L limbs
   u32 t[2 * L];
-  if constexpr (KARA) {
-    kara_mul<L>(t, as, b);
-  } else {
-    u64 acc = 0;
-    u32 hi = 0;
-#pragma unroll
-    for (int k = 0; k < 2 * L - 1; k++) {
-#pragma unroll
-      for (int i = (k < L ? 0 : k - L + 1); i <= (k < L ? k : L - 1); i++) mac_vv(acc, hi, as[i], b[k - i]);
-      t[k] = (u32)acc;
-      shift_col(acc, hi);
-    }
-    t[2 * L - 1] = (u32)acc;
-  }
+  kara_mul<L>(t, as, b);
   // r1 = t >> (M - 2) = t >> (32(L-1) + 26): limbs L-1 .. 2L-1, bit offset 26
   u32 r1[L];
 #pragma unroll
   for (int i = 0; i < L; i++) r1[i] = __builtin_amdgcn_alignbit(t[L + i], t[L - 1 + i], 26);
   // r2 = (r1 * mu) >> (M + 5) = >> (32L + 1): need product limbs L .. 2L-1 exactly
   u32 p[2 * L];
-  if constexpr (KARA) {
-    u32 muv[L];
-    to_vgprs<L>(muv, c.mu);
-    kara_mul<L>(p, r1, muv);
-  } else {
-    u64 acc = 0;
-    u32 hi = 0;
-#pragma unroll
-    for (int k = 0; k < 2 * L - 1; k++) {
-#pragma unroll
-      for (int i = (k < L ? 0 : k - L + 1); i <= (k < L ? k : L - 1); i++) mac_vs(acc, hi, r1[i], c.mu[k - i]);
-      p[k] = (u32)acc;
-      shift_col(acc, hi);
-    }
-    p[2 * L - 1] = (u32)acc;
-  }
+  u32 muv[L];
+  to_vgprs<L>(muv, c.mu);
+  kara_mul<L>(p, r1, muv);
   u32 r2[L];
 #pragma unroll
   for (int i = 0; i < L - 1; i++) r2[i] = __builtin_amdgcn_alignbit(p[L + i + 1], p[L + i], 1);

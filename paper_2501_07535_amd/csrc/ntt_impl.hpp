@@ -786,7 +786,7 @@ inline NttC<L, FW> make_consts(const FieldRaw& f, const DigitConsts& dc) {
   NttC<L, FW> c;
   for (int j = 0; j < Digits<L, FW>::D; j++) {
     c.qd[j] = dc.qd[j];
-    c.nqd[j] = dc.nqd[j];
+    c.nqd[j] = f.nqd[j];
   }
   c.qinvd = dc.qinvd;
   u64 carry = 0;

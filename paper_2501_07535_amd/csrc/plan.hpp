@@ -18,9 +18,10 @@ struct FieldEntry {
   DigitConsts dc;
   HBig Q, one_m;
   HBig adj;  // 2^(bD) mod q: R of the digit form
-  // last axpy scalar, cached with its Montgomery form
+  // last axpy scalar, cached with its digits and its quotient's
   std::vector<uint32_t> alpha_key;
-  std::vector<uint32_t> alpha_m;
+  uint32_t alpha_d[40] = {0};
+  uint32_t alpha_q[40] = {0};
 };
 
 struct DirTables {
@@ -82,14 +83,14 @@ struct BlasJobRec {
   uint32_t* out;
   uint64_t n;
 };
-size_t blas_consts_bytes(int L);
+size_t blas_consts_bytes(int L, bool fw);
 void blas_fill_consts(const FieldRaw& f, const BlasArgs& a, void* dst);
 int launch_blas_batch(int op, int L, uint32_t variant, bool fw, const void* recs, const void* consts,
                       const uint2* items, uint32_t nitems, hipStream_t s);
 // vmul's product variant for a compute limb count (capi.cpp)
 uint32_t vmul_variant(int L);
-// alpha (storage limbs words) in Montgomery form for axpy, validated < q
-int axpy_alpha(FieldEntry& fe, const uint32_t* alpha, uint32_t limbs, uint32_t* alpha_m);
+// alpha (storage limbs words), validated < q, as axpy's digits and quotient in *a
+int axpy_alpha(FieldEntry& fe, const uint32_t* alpha, uint32_t limbs, BlasArgs* a);
 // n pseudo-random residues below q in Ls = f.Ls storage planes (timing inputs for the tuners)
 int fill_random_residues(const FieldRaw& f, uint32_t* d, uint64_t n, uint32_t seed, hipStream_t s);
 int launch_fill_residues(uint32_t* p, uint64_t n, int planes, int top, uint32_t top_mask, uint32_t seed, hipStream_t s);

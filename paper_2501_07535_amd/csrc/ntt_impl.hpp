@@ -282,14 +282,20 @@ __device__ __forceinline__ void ntt_round(u32* lds, const TileGeo& t, u32 sg0, c
     u32 p0 = lb * B + (v & (sub - 1));
     u32 x[1 << R][L];
     const u32 idx0 = p0 * t.C + g, step = sub << t.logc;  // the unit's elements in LDS
-    // LOADG: the first stage's twiddle (one per unit) is loaded before the
-    // elements, and the elements pair by pair of the first stage, (e, e +
-    // 2^(R-1)): a wave's loads complete in issue order, so the first pair's
-    // butterfly can start while the later pairs are still in flight
+    // The first stage's twiddle (one per unit) is loaded before the elements
+    // where it is what a wave waits for longest: in radix-2 units, which run
+    // where few waves share a SIMD (256 bits, 2^16 points 27.0 -> 26.1 us; 128
+    // bits, 2^12 12.5 -> 11.5), and with LOADG, where the elements come pair by
+    // pair of the first stage, (e, e + 2^(R-1)): a wave's loads complete in
+    // issue order, so the first pair's butterfly can start while the later pairs
+    // are still in flight.  (With radix-4 units from LDS: 2^20 points 116 -> 117 us.
+    // Loaded a round ahead, before the barrier, it was 10% slower: the value
+    // crosses the loop over units, and the compiler waits for it there.)
+    constexpr bool EARLY = R == 1 || LOADG;
     const u32 toff = tw_off(t, sg0, lb, g);
     Twiddle<L, FW> w;
+    if constexpr (EARLY && !FIRST) w.load(tw, t.n, tw_first(t, sg0, 0, 0), toff);
     if constexpr (LOADG) {
-      if constexpr (!FIRST) w.load(tw, t.n, tw_first(t, sg0, 0, 0), toff);
       const u32 src = row_off(t, p0, g, t.K == 0) << 2;
 #pragma unroll
       for (int pp = 0; pp < (1 << R); pp++) {
@@ -308,7 +314,7 @@ __device__ __forceinline__ void ntt_round(u32* lds, const TileGeo& t, u32 sg0, c
 #pragma unroll
       for (int i = 0; i < (1 << s); i++) {
         const bool one = FIRST && i == 0;
-        if (!one && !(LOADG && s == 0)) w.load(tw, t.n, tw_first(t, sg0, s, i), toff);
+        if (!one && !(EARLY && s == 0)) w.load(tw, t.n, tw_first(t, sg0, s, i), toff);
 #pragma unroll
         for (int e = 2 * half * i; e < 2 * half * i + half; e++) {
           if (one) {
@@ -501,7 +507,11 @@ __device__ __forceinline__ void pass_tile(u32* lds, const NttPassArgs& a, const 
   // Up to 8 limbs each lane moves 4 consecutive words per limb: 4 groups of one
   // row when the tile has C >= 4 groups, else 4 consecutive rows of a one-pass
   // transform; wider limbs (4 L live words) take one element per lane.
-  const bool vec_g = t.C >= 4, vec_u = (t.C == 1 && t.S == 1 && t.rows >= 4);
+  // Radix-2 units have up to half as many threads as elements; where 4 elements
+  // per lane would leave threads idle, they take one each as well (256 bits:
+  // 2^10 points 15.2 -> 14.5 us, 2^12 18.4 -> 17.6).
+  const bool busy = R > 1 || (t.E >> 2) >= T;
+  const bool vec_g = t.C >= 4 && busy, vec_u = t.C == 1 && t.S == 1 && t.rows >= 4 && busy;
   if (direct) {
     // the first round loads its own elements
   } else if (L <= 8 && (vec_g || vec_u)) {
@@ -621,7 +631,7 @@ __device__ __forceinline__ void pass_tile(u32* lds, const NttPassArgs& a, const 
       for (int j = 0; j < L; j++)
         *reinterpret_cast<uint4*>(a.out + (u64)j * n + dst) = make_uint4(x[0][j], x[1][j], x[2][j], x[3][j]);
     }
-  } else if (kVecStore && t.K == 0 && t.rows >= 4) {
+  } else if (kVecStore && t.K == 0 && t.rows >= 4 && busy) {
     // 4 consecutive output addresses inside one group's run of 2^k
     for (u32 e4 = tid; e4 < (t.E >> 2); e4 += T) {
       u32 e = e4 << 2;

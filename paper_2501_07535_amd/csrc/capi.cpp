@@ -98,6 +98,16 @@ int build_field(const uint32_t* q, uint32_t limbs, std::shared_ptr<FieldEntry>* 
     int b = digit_bits(f.L), D = digit_count(f.L, f.fw);
     digits_of(Q, f.L, f.fw, dc.qd);
     digits_of(HBig::sub(HBig::pow2(b * D), Q), f.L, f.fw, f.nqd);
+    if (!f.fw) {
+      // quotient estimates of the lazy butterflies
+      uint32_t carry = 0;
+      for (int i = 0; i < f.L; i++) {
+        const uint64_t v = (uint64_t)f.q[i] + carry;
+        f.qsw[i] = (uint32_t)v;
+        carry = v >> 31 ? 1u : 0u;  // taken as signed, the word is short by 2^32
+      }
+      f.cinv = (uint32_t)((1ull << 58) / ((uint64_t)f.qn[f.L - 1] + 1));
+    }
     // vmul: the modulus scaled to bD - 1 bits
     f.vd = (uint32_t)((f.fw ? 32 * f.L : 32 * f.L - 4) - M);
     HBig qs = HBig::shl(Q, (int)f.vd + barrett_off(f.L, f.fw)), vmu;

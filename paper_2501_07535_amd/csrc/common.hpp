@@ -58,6 +58,8 @@ struct FieldRaw {
   uint32_t vmu[40];        // and its quotient constant, the top digit with the bits above bD
   uint32_t vnqn[40];       // 2^(bD) minus the scaled modulus, in digits
   uint32_t nqd[40];        // 2^(bD) - q in digits
+  uint32_t qsw[kMaxLimbs]; // q in signed words: the sum of (int32) qsw[i] 2^(32 i)
+  uint32_t cinv;           // floor(2^58 / (qt + 1)), qt the top 32 bits of q 2^d (2^27 <= qt < 2^28)
 };
 
 enum BlasOp { OP_VADD = 0, OP_VSUB = 1, OP_VMUL = 2, OP_AXPY = 3 };
@@ -124,7 +126,7 @@ struct NttSchedule {
 
 // arithmetic of a transform kernel: lazy butterflies with the schoolbook or
 // the Karatsuba digit product, or canonical ones for a full-width modulus
-enum NttArith { kArithLazy = 0, kArithFull = 1, kArithKara = 2 };
+enum NttArith { kArithLazy = 0, kArithFull = 1, kArithKara = 2, kArithOffset = 3 };
 
 
 // per-modulus constants of the digit-form multiplies

@@ -608,9 +608,8 @@ __device__ __forceinline__ void to_vgprs(u32* dst, const u32* src) {
   for (int i = 0; i < L; i++) asm volatile("v_mov_b32 %0, %1" : "=v"(dst[i]) : "s"(src[i]));
 }
 
-// Lazy butterfly with twiddle 1 (the first stages of a transform): the same
-// residues as the multiplying butterfly, with t = y mod 2q in [0, 2q) in place
-// of the Montgomery product w*y.
+// Harvey's lazy butterfly with twiddle 1 (the first stages of a transform), with
+// t = y mod 2q in [0, 2q) in place of the product w*y.
 template <int L>
 __device__ __forceinline__ void ct_butterfly_one(u32* x, u32* y, const u32* q2v) {
   u32 xr[L], t[L], d[L], s[L];
@@ -623,12 +622,47 @@ __device__ __forceinline__ void ct_butterfly_one(u32* x, u32* y, const u32* q2v)
   add_vv<L>(y, d, q2v);
 }
 
-// Cooley-Tukey butterfly with lazy reduction (Harvey, "Faster arithmetic for
-// number-theoretic transforms", J. Symb. Comp. 2014): inputs and outputs in
-// [0, 4q), q2 = 2q.
-//   x <- x mod 2q;  t <- w*y in [0, 2q);  x' = x + t;  y' = x - t + 2q.
-// Same residues as (x + wy, x - wy) mod q; 5L add-class ops instead of 8L.
-// Here the additions, once the product t = w*y in [0, 2q) is known.
+// Lazy butterflies.  With 4 spare bits above q (and digits that cover all 32L
+// bits: spare_bits, every headroom limb count but 10) a value may be anything
+// in [0, 16q), and a multiplying butterfly is two additions,
+//   t <- w*y in [0, g q);  x' = x + t;  y' = x - t,   g = 1 + 2^(32L-bD) + 2^-24,
+// as long as x stays between t and 16q - t: stages move the bounds by g q each
+// way (growth_64th, in 64ths).  Where the next stages would leave [0, 16q), the
+// x of the first of them are moved to [7q, 8q] (offset_reduce): with five or six
+// stages in a pass that is once per pass, against a trial subtraction of x and
+// an addition of 2q in every butterfly (Harvey, "Faster arithmetic for
+// number-theoretic transforms", J. Symb. Comp. 2014: values in [0, 4q)).
+constexpr int spare_bits(int L) { return digit_bits(L) * digit_count(L) - 32 * L; }
+constexpr u32 growth_of(int spare) { return 64 + (64 >> (spare < 0 ? 0 : spare < 6 ? spare : 6)) + 1; }
+template <int L>
+constexpr u32 growth_64th = growth_of(spare_bits(L));
+
+// r = x - (f - off) q for x in [0, 16q), where f is floor(x / q) or, when x / q
+// is within 2^-24 above it, one less: r in [off q, (off + 1 + 2^-24) q).  f comes
+// from the top 32 bits of x 2^d; the multiple of q is formed in signed words.
+template <int L>
+__device__ __forceinline__ void offset_reduce(u32* x, u32 off, const u32* qsw, u32 d, u32 cinv) {
+  u32 xt;
+  if constexpr (L == 1)
+    xt = x[0] << d;
+  else
+    xt = (u32)((((u64)x[L - 1] << 32 | x[L - 2]) << d) >> 32);
+  const int k = (int)(off - (__umulhi(xt, cinv) >> 26));
+  u32 p[L];
+  int64_t acc = 0;
+#pragma unroll
+  for (int i = 0; i < L; i++) {
+    acc = (acc >> 32) + (int64_t)k * (int32_t)qsw[i];
+    p[i] = (u32)acc;
+  }
+  u32 r[L];
+  add_vv<L>(r, x, p);
+#pragma unroll
+  for (int i = 0; i < L; i++) x[i] = r[i];
+}
+
+// Harvey's form of the additions, t = w*y in [0, 2q) known:
+//   x <- x mod 2q;  x' = x + t;  y' = x - t + 2q.
 template <int L>
 __device__ __forceinline__ void ct_lazy_tail(u32* x, u32* y, const u32* t, const u32* q2v) {
   u32 xr[L], d[L], s[L];
@@ -639,22 +673,48 @@ __device__ __forceinline__ void ct_lazy_tail(u32* x, u32* y, const u32* t, const
   add_vv<L>(y, d, q2v);
 }
 
-// Lazy butterfly with the twiddle and its quotient in digits, 2q in VGPRs.
-template <int L>
-__device__ __forceinline__ void ct_butterfly_digits(u32* x, u32* y, const u32* w, const u32* wq, const u32* nqd,
-                                                    const u32* q2v) {
-  u32 t[L];
-  quot_mul<L>(t, y, w, wq, nqd);
-  ct_lazy_tail<L>(x, y, t, q2v);
+// The additions of a lazy butterfly.  FIRST (the transform's first round, which
+// starts from canonical x below what an offset needs): x' = x + t, y' = x - t + 2q.
+template <int L, bool OFF, bool FIRST>
+__device__ __forceinline__ void ct_tail(u32* x, u32* y, const u32* t, const u32* q2v) {
+  if constexpr (!OFF) {
+    ct_lazy_tail<L>(x, y, t, q2v);
+  } else {
+    u32 s[L], d[L];
+    add_vv<L>(s, x, t);
+    sub_vv<L>(d, x, t);
+    if constexpr (FIRST) {
+      add_vv<L>(y, d, q2v);
+    } else {
+#pragma unroll
+      for (int i = 0; i < L; i++) y[i] = d[i];
+    }
+#pragma unroll
+    for (int i = 0; i < L; i++) x[i] = s[i];
+  }
 }
 
-// The same with the Karatsuba form of the product w y.
+// (x + y, x - y + cq) for x, y below cq: the first round's pairs with twiddle 1
 template <int L>
-__device__ __forceinline__ void ct_butterfly_kara(u32* x, u32* y, const u32* w, const u32* wq, const u32* nqd,
-                                                  const u32* q2v) {
+__device__ __forceinline__ void ct_one_tail(u32* x, u32* y, const u32* cqv) {
+  u32 s[L], d[L];
+  add_vv<L>(s, x, y);
+  sub_vv<L>(d, x, y);
+  add_vv<L>(y, d, cqv);
+#pragma unroll
+  for (int i = 0; i < L; i++) x[i] = s[i];
+}
+
+// Multiplying butterfly, the product w y by schoolbook or (KARA) Karatsuba columns.
+template <int L, bool KARA, bool OFF, bool FIRST>
+__device__ __forceinline__ void ct_butterfly_mul(u32* x, u32* y, const u32* w, const u32* wq, const u32* nqd,
+                                                 const u32* q2v) {
   u32 t[L];
-  quot_mul_kara<L>(t, y, w, wq, nqd);
-  ct_lazy_tail<L>(x, y, t, q2v);
+  if constexpr (KARA)
+    quot_mul_kara<L>(t, y, w, wq, nqd);
+  else
+    quot_mul<L>(t, y, w, wq, nqd);
+  ct_tail<L, OFF, FIRST>(x, y, t, q2v);
 }
 
 // The same for a full-width modulus: t (with its carry word) reduced, then

@@ -26,8 +26,9 @@
 //     first m powers of w_{2m}).  With that order the C
 //     groups of a tile read C consecutive entries, and the first pass reads a
 //     table prefix shared by every tile.
-// Butterflies use lazy reduction: values stay in [0, 4q) between stages and
-// between passes, and the last pass stores canonical residues in [0, q).
+// Butterflies use lazy reduction: values stay in [0, 4q) or [0, 16q)
+// (offset_applies) between stages and between passes, and the last pass stores
+// canonical residues in [0, q).
 #pragma once
 #include <string.h>
 
@@ -38,9 +39,29 @@
 
 namespace moma {
 
+// Which kernels take the offset form of the lazy butterflies (OFF).  It issues
+// fewer additions per butterfly, but its reductions are a serial chain, while a
+// wave that has its SIMD almost to itself fits Harvey's independent additions
+// between its products.  So: radix-4 units from 6 limbs (2^20 points: 256 bits
+// 115.6 -> 113 us, 512 bits 375 -> 315, 160 bits 71.4 -> 72), radix-2 units from
+// 20 (2^16 points: 640 bits 66.3 -> 63.9 us, 1024 bits 125 -> 118; but 512 bits 46.0
+// -> 51.0, 256 bits 26.4 -> 28.0); the Karatsuba kernels keep Harvey's.
+constexpr bool offset_applies(int L, int R) {
+  return spare_bits(L) >= 0 && ((R == 2 && L >= 6) || (R == 1 && L >= 20));
+}
+
+// constants of the offset form, in the kernels of limb counts that have it
+template <int L, bool OFF>
+struct OffsetC {};
+template <int L>
+struct OffsetC<L, true> {
+  u32 qsw[L];  // q in signed words
+  u32 d, cinv;  // quotient estimate (offset_reduce)
+};
+
 // FW: a full-width modulus (no headroom): canonical values, digits over 32L bits
 template <int L, bool FW = false>
-struct NttC {
+struct NttC : OffsetC<L, !FW && (offset_applies(L, 1) || offset_applies(L, 2))> {
   u32 q[L];
   u32 q2[L];                        // 2q (unused for a full-width modulus)
   u32 qinv;
@@ -162,8 +183,9 @@ __device__ __forceinline__ void hbm_put(const u32* x, u32* first, u64 n, u32 lan
 // What the last pass does to its N elements before it stores them.  The
 // inverse's factor is read here, by uniform loads, and not held in registers
 // from the kernel's start.
-template <int L, bool FW, int N>
-__device__ __forceinline__ void finish_elems(u32 (*x)[L], const NttPassArgs& a, const NttC<L, FW>& c) {
+template <int L, int AR, int N>
+__device__ __forceinline__ void finish_elems(u32 (*x)[L], const NttPassArgs& a, const NttC<L, AR == kArithFull>& c) {
+  constexpr bool FW = AR == kArithFull;
   if (!a.last) return;
   if (a.scale) {
     constexpr int D = Digits<L, FW>::D;
@@ -179,7 +201,7 @@ __device__ __forceinline__ void finish_elems(u32 (*x)[L], const NttPassArgs& a, 
 #pragma unroll
     for (int e = 0; e < N; e++) {
       u32 y[L], top;
-      quot_mul<L, FW>(y, x[e], sd, sq, c.nqd, &top);  // x < 4q (q, full width): y in [0, 2q)
+      quot_mul<L, FW>(y, x[e], sd, sq, c.nqd, &top);  // y in [0, 2q)
       if constexpr (FW)
         reduce_top<L>(x[e], y, top, c.q);
       else
@@ -189,8 +211,14 @@ __device__ __forceinline__ void finish_elems(u32 (*x)[L], const NttPassArgs& a, 
 #pragma unroll
     for (int e = 0; e < N; e++) {
       u32 y[L];
-      reduce_once<L>(y, x[e], c.q2);  // [0, 4q) -> [0, 2q)
-      reduce_once<L>(x[e], y, c.q);   // -> [0, q)
+      if constexpr (AR == kArithOffset) {
+        offset_reduce<L>(x[e], 0, c.qsw, c.d, c.cinv);  // [0, 16q) -> [0, 2q)
+#pragma unroll
+        for (int j = 0; j < L; j++) y[j] = x[e][j];
+      } else {
+        reduce_once<L>(y, x[e], c.q2);  // [0, 4q) -> [0, 2q)
+      }
+      reduce_once<L>(x[e], y, c.q);  // -> [0, q)
     }
   }
 }
@@ -204,10 +232,14 @@ __device__ __forceinline__ void finish_elems(u32 (*x)[L], const NttPassArgs& a, 
 // VGPRs for the additions; neither is live across the multiply.
 constexpr int kLateLoadLimbs = 11;
 
+// multiple of q the reduced x of a round get (offset_reduce): the most stages
+// fit below and above it
+constexpr u32 kOffset = 7;
+
 template <int L, bool FIRST, bool STORE, int AR>
 __device__ __forceinline__ void round_late(u32* lds, const TileGeo& t, u32 sg0, const NttPassArgs& a,
-                                           const NttC<L, AR == kArithFull>& c) {
-  constexpr bool FW = AR == kArithFull;
+                                           const NttC<L, AR == kArithFull>& c, bool red) {
+  constexpr bool FW = AR == kArithFull, OFF = AR == kArithOffset;
   const u32* __restrict__ tw = a.tw;
   const u32 k = t.k;
   const u32 B = 1u << (k - sg0);  // block size (rows) at stage sg0; the pair is B/2 rows apart
@@ -223,9 +255,11 @@ __device__ __forceinline__ void round_late(u32* lds, const TileGeo& t, u32 sg0, 
       lds_get<L>(x, lds, t.E, r0 * t.C + g);
       lds_get<L>(y, lds, t.E, r1 * t.C + g);
       u32 qv[L];
-      to_vgprs<L>(qv, FW ? c.q : c.q2);
+      to_vgprs<L>(qv, FW || OFF ? c.q : c.q2);
       if constexpr (FW)
         ct_butterfly_one_fw<L>(x, y, qv);
+      else if constexpr (OFF)
+        ct_one_tail<L>(x, y, qv);
       else
         ct_butterfly_one<L>(x, y, qv);
     } else {
@@ -233,24 +267,26 @@ __device__ __forceinline__ void round_late(u32* lds, const TileGeo& t, u32 sg0, 
       u32 p[L], top = 0;
       w.load(tw, t.n, tw_first(t, sg0, 0, 0), tw_off(t, sg0, lb, g));
       lds_get<L>(y, lds, t.E, r1 * t.C + g);
-      if constexpr (FW)
-        quot_mul<L, true>(p, y, w.w(), w.wq(), c.nqd, &top);
-      else if constexpr (AR == kArithKara)
+      if constexpr (AR == kArithKara)
         quot_mul_kara<L>(p, y, w.w(), w.wq(), c.nqd);
       else
-        quot_mul<L>(p, y, w.w(), w.wq(), c.nqd);
+        quot_mul<L, FW>(p, y, w.w(), w.wq(), c.nqd, &top);
       lds_get<L>(x, lds, t.E, r0 * t.C + g);
       u32 qv[L];
-      to_vgprs<L>(qv, FW ? c.q : c.q2);
-      if constexpr (FW)
+      if constexpr (FIRST || !OFF) to_vgprs<L>(qv, FW ? c.q : c.q2);
+      if constexpr (FW) {
         ct_fw_tail<L>(x, y, p, top, qv);
-      else
-        ct_lazy_tail<L>(x, y, p, qv);
+      } else {
+        if constexpr (OFF && !FIRST) {
+          if (red) offset_reduce<L>(x, kOffset, c.qsw, c.d, c.cinv);
+        }
+        ct_tail<L, OFF, FIRST>(x, y, p, qv);
+      }
     }
     if constexpr (STORE) {
       const u32 dst = row_off(t, r0, g, false) << 2;
-      finish_elems<L, FW, 1>(&x, a, c);
-      finish_elems<L, FW, 1>(&y, a, c);
+      finish_elems<L, AR, 1>(&x, a, c);
+      finish_elems<L, AR, 1>(&y, a, c);
       hbm_put<L>(x, a.out, t.n, dst);
       hbm_put<L>(y, a.out + (1ull << (t.K + sg0)), t.n, dst);
     } else {
@@ -261,21 +297,23 @@ __device__ __forceinline__ void round_late(u32* lds, const TileGeo& t, u32 sg0, 
 }
 
 // AR: the kernel's arithmetic (NttArith)
+// red: the x of the round's first stage are reduced before it (OFF)
 template <int L, int R, bool FIRST, bool STORE, bool LOADG = false, int AR = kArithLazy>
 __device__ __forceinline__ void ntt_round(u32* lds, const TileGeo& t, u32 sg0, const NttPassArgs& a,
-                                          const NttC<L, AR == kArithFull>& c) {
-  constexpr bool FW = AR == kArithFull;
+                                          const NttC<L, AR == kArithFull>& c, bool red) {
+  constexpr bool FW = AR == kArithFull, OFF = AR == kArithOffset;
   const u32* __restrict__ tw = a.tw;
   const u32 k = t.k;
   const u32 B = 1u << (k - sg0);        // block size (rows) at stage sg0
   const u32 sub = B >> R;                // row spacing of a unit's elements
   const u32 units = (t.E >> R);
   if constexpr (R == 1 && !LOADG && L >= kLateLoadLimbs) {
-    round_late<L, FIRST, STORE, AR>(lds, t, sg0, a, c);
+    round_late<L, FIRST, STORE, AR>(lds, t, sg0, a, c, red);
     return;
   }
-  u32 q2v[L];  // 2q (lazy butterflies), or q (full width)
-  to_vgprs<L>(q2v, FW ? c.q : c.q2);
+  u32 q2v[L], q1v[L];  // 2q (lazy butterflies), or q (full width); q in the first round
+  if constexpr (FIRST || !OFF) to_vgprs<L>(q2v, FW ? c.q : c.q2);
+  if constexpr (FIRST && OFF) to_vgprs<L>(q1v, c.q);
   for (u32 b = threadIdx.x; b < units; b += blockDim.x) {
     u32 g = b & (t.C - 1), v = b >> t.logc;
     u32 lb = v >> (k - sg0 - R);
@@ -288,10 +326,10 @@ __device__ __forceinline__ void ntt_round(u32* lds, const TileGeo& t, u32 sg0, c
     // bits, 2^12 12.5 -> 11.5), and with LOADG, where the elements come pair by
     // pair of the first stage, (e, e + 2^(R-1)): a wave's loads complete in
     // issue order, so the first pair's butterfly can start while the later pairs
-    // are still in flight.  (With radix-4 units from LDS: 2^20 points 116 -> 117 us.
+    // are still in flight; and before the branch that may reduce x (OFF).  (With radix-4 units from LDS: 2^20 points 116 -> 117 us.
     // Loaded a round ahead, before the barrier, it was 10% slower: the value
     // crosses the loop over units, and the compiler waits for it there.)
-    constexpr bool EARLY = R == 1 || LOADG;
+    constexpr bool EARLY = R == 1 || LOADG || OFF;
     const u32 toff = tw_off(t, sg0, lb, g);
     Twiddle<L, FW> w;
     if constexpr (EARLY && !FIRST) w.load(tw, t.n, tw_first(t, sg0, 0, 0), toff);
@@ -307,34 +345,40 @@ __device__ __forceinline__ void ntt_round(u32* lds, const TileGeo& t, u32 sg0, c
 #pragma unroll
       for (int e = 0; e < (1 << R); e++) lds_get<L>(x[e], lds, t.E, idx0 + e * step);
     }
+    if constexpr (OFF && !FIRST) {
+      if (red)
+#pragma unroll
+        for (int e = 0; e < (1 << (R - 1)); e++) offset_reduce<L>(x[e], kOffset, c.qsw, c.d, c.cinv);
+    }
 #pragma unroll
     for (int s = 0; s < R; s++) {
       const int half = 1 << (R - 1 - s);
       // block i of the 2^s the unit has at this stage: one twiddle, `half` pairs (e, e + half)
 #pragma unroll
       for (int i = 0; i < (1 << s); i++) {
-        const bool one = FIRST && i == 0;
+        // (OFF: sums without a product double the bound, so two stages of them at most)
+        const bool one = FIRST && i == 0 && (!OFF || s < 2);
         if (!one && !(EARLY && s == 0)) w.load(tw, t.n, tw_first(t, sg0, s, i), toff);
 #pragma unroll
         for (int e = 2 * half * i; e < 2 * half * i + half; e++) {
           if (one) {
             if constexpr (FW)
               ct_butterfly_one_fw<L>(x[e], x[e + half], q2v);
+            else if constexpr (OFF)
+              ct_one_tail<L>(x[e], x[e + half], s == 0 ? q1v : q2v);
             else
               ct_butterfly_one<L>(x[e], x[e + half], q2v);
           } else if constexpr (FW) {
             ct_butterfly_fw<L>(x[e], x[e + half], w.w(), w.wq(), c.nqd, q2v);
-          } else if constexpr (AR == kArithKara) {
-            ct_butterfly_kara<L>(x[e], x[e + half], w.w(), w.wq(), c.nqd, q2v);
           } else {
-            ct_butterfly_digits<L>(x[e], x[e + half], w.w(), w.wq(), c.nqd, q2v);
+            ct_butterfly_mul<L, AR == kArithKara, OFF, FIRST>(x[e], x[e + half], w.w(), w.wq(), c.nqd, q2v);
           }
         }
       }
     }
     if constexpr (STORE) {
       const u32 dst = row_off(t, p0, g, false) << 2;
-      finish_elems<L, FW, (1 << R)>(x, a, c);
+      finish_elems<L, AR, (1 << R)>(x, a, c);
 #pragma unroll
       for (int e = 0; e < (1 << R); e++) hbm_put<L>(x[e], a.out + ((u64)rev_bits(e, R) << (t.K + sg0)), t.n, dst);
     } else {
@@ -371,9 +415,10 @@ __device__ __forceinline__ void swap_with_partner(u32& a, u32& b, bool c32) {
 // 2j + 2^R h and 2j + 2^R h + 1 of the block, whose last-stage block index is
 // 2^R lb + 2^(R-1) h + j.  Requires C in {16, 32}, whole wavefronts of units,
 // and a round that is not the transform's first.
-template <int L, int R, bool STORE>
+template <int L, int R, bool STORE, int AR>
 __device__ __forceinline__ void ntt_round_last(u32* lds, const TileGeo& t, u32 sg0, const NttPassArgs& a,
-                                               const NttC<L>& c) {
+                                               const NttC<L>& c, bool red) {
+  constexpr bool OFF = AR == kArithOffset;
   const u32* __restrict__ tw = a.tw;
   const u32 k = t.k;
   const u32 B = 1u << (k - sg0);        // block size (rows) at stage sg0: 2^(R+1)
@@ -381,7 +426,7 @@ __device__ __forceinline__ void ntt_round_last(u32* lds, const TileGeo& t, u32 s
   const bool c32 = t.logc == 5;
   constexpr int H = 1 << (R - 1);
   u32 q2v[L];
-  to_vgprs<L>(q2v, c.q2);
+  if constexpr (!OFF) to_vgprs<L>(q2v, c.q2);
   for (u32 b = threadIdx.x; b < units; b += blockDim.x) {
     u32 g = b & (t.C - 1), v = b >> t.logc;
     u32 lb = v >> 1;
@@ -389,18 +434,24 @@ __device__ __forceinline__ void ntt_round_last(u32* lds, const TileGeo& t, u32 s
     const u32 toff = tw_off(t, sg0, lb, g);
     u32 x[1 << R][L];
     const u32 step = 2u << t.logc;
+    Twiddle<L> w;
+    if constexpr (OFF) w.load(tw, t.n, tw_first(t, sg0, 0, 0), toff);
 #pragma unroll
     for (int e = 0; e < (1 << R); e++) lds_get<L>(x[e], lds, t.E, p0 * t.C + g + e * step);
-    Twiddle<L> w;
+    if constexpr (OFF) {
+      if (red)
+#pragma unroll
+        for (int e = 0; e < H; e++) offset_reduce<L>(x[e], kOffset, c.qsw, c.d, c.cinv);
+    }
 #pragma unroll
     for (int s = 0; s < R; s++) {
       const int half = 1 << (R - 1 - s);
 #pragma unroll
       for (int i = 0; i < (1 << s); i++) {
-        w.load(tw, t.n, tw_first(t, sg0, s, i), toff);
+        if (!OFF || s > 0) w.load(tw, t.n, tw_first(t, sg0, s, i), toff);
 #pragma unroll
         for (int e = 2 * half * i; e < 2 * half * i + half; e++)
-          ct_butterfly_digits<L>(x[e], x[e + half], w.w(), w.wq(), c.nqd, q2v);
+          ct_butterfly_mul<L, false, OFF, false>(x[e], x[e + half], w.w(), w.wq(), c.nqd, q2v);
       }
     }
 #pragma unroll
@@ -412,13 +463,13 @@ __device__ __forceinline__ void ntt_round_last(u32* lds, const TileGeo& t, u32 s
     for (int jp = 0; jp < H; jp++) {
       // last-stage block 2^R lb + 2^(R-1) h + jp: h reverses to the lowest bit
       w.load(tw, t.n, tw_first(t, sg0, R, (u32)jp), toff + (h << (t.K + sg0)));
-      ct_butterfly_digits<L>(x[jp], x[jp + H], w.w(), w.wq(), c.nqd, q2v);
+      ct_butterfly_mul<L, false, OFF, false>(x[jp], x[jp + H], w.w(), w.wq(), c.nqd, q2v);
     }
     const u32 r0 = lb * B + (h << R);
     if constexpr (STORE) {
       // row r0 + 2 jp + o: its low R bits reverse to the top of the k
       const u32 dst = row_off(t, r0, g, false) << 2;
-      finish_elems<L, false, (1 << R)>(x, a, c);
+      finish_elems<L, AR, (1 << R)>(x, a, c);
 #pragma unroll
       for (int jp = 0; jp < H; jp++)
 #pragma unroll
@@ -442,24 +493,26 @@ constexpr bool kFuseStore = L <= (FW ? 9 : 10);
 
 template <int L, int R, int AR = kArithLazy>
 __device__ __forceinline__ void round_at(u32* lds, const TileGeo& t, u32 sg0, const NttPassArgs& a,
-                                         const NttC<L, AR == kArithFull>& c, bool store) {
+                                         const NttC<L, AR == kArithFull>& c, bool store, bool red) {
   if constexpr (kFuseStore<L, AR == kArithFull>) {
     if (store) {
-      ntt_round<L, R, false, true, false, AR>(lds, t, sg0, a, c);
+      ntt_round<L, R, false, true, false, AR>(lds, t, sg0, a, c, red);
       return;
     }
   }
   if (t.K == 0 && sg0 == 0)
-    ntt_round<L, R, true, false, false, AR>(lds, t, sg0, a, c);
+    ntt_round<L, R, true, false, false, AR>(lds, t, sg0, a, c, false);
   else
-    ntt_round<L, R, false, false, false, AR>(lds, t, sg0, a, c);
+    ntt_round<L, R, false, false, false, AR>(lds, t, sg0, a, c, red);
 }
 
 // Fused pointwise product of a cyclic product's first inverse pass:
 // r = x * y * 2^(-bD) mod q in [0, 2q) for x, y < q (the digit-form multiply
 // with y converted to digits; the last pass's scale constant carries 2^(bD)).
-template <int L, bool FW = false>
-__device__ __forceinline__ void pointwise_digits(u32* r, const u32* x, const u32* y, const NttC<L, FW>& c) {
+template <int L, int AR>
+__device__ __forceinline__ void pointwise_digits(u32* r, const u32* x, const u32* y,
+                                                 const NttC<L, AR == kArithFull>& c) {
+  constexpr bool FW = AR == kArithFull;
   u32 yd[Digits<L, FW>::D];
   to_digits<L, FW>(yd, y);
   if constexpr (FW) {
@@ -468,7 +521,14 @@ __device__ __forceinline__ void pointwise_digits(u32* r, const u32* x, const u32
     mont_mul_digits<L, true>(t, x, yd, c.qd, c.qinvd, &top);
     reduce_top<L>(r, t, top, c.q);
   } else {
-    mont_mul_digits<L>(r, x, yd, c.qd, c.qinvd);
+    u32 t[L];
+    mont_mul_digits<L>(t, x, yd, c.qd, c.qinvd);
+    if constexpr (AR == kArithOffset) {
+      reduce_once<L>(r, t, c.q);  // the first round's bounds start from [0, q)
+    } else {
+#pragma unroll
+      for (int j = 0; j < L; j++) r[j] = t[j];
+    }
   }
 }
 
@@ -480,6 +540,7 @@ template <int L, int R, bool MUL, bool LASTX = false, int AR = kArithLazy>
 __device__ __forceinline__ void pass_tile(u32* lds, const NttPassArgs& a, const NttC<L, AR == kArithFull>& c,
                                           u64 tile) {
   constexpr bool FW = AR == kArithFull;
+  constexpr int AX = AR == kArithLazy && offset_applies(L, R) ? kArithOffset : AR;
   static_assert(AR == kArithLazy || !LASTX, "only the lazy schoolbook kernels have the cross-lane variant");
   TileGeo t;
   t.k = a.k;
@@ -533,7 +594,7 @@ __device__ __forceinline__ void pass_tile(u32* lds, const NttPassArgs& a, const 
           y[0][j] = z.x; y[1][j] = z.y; y[2][j] = z.z; y[3][j] = z.w;
         }
 #pragma unroll
-        for (int q4 = 0; q4 < 4; q4++) pointwise_digits<L, FW>(r[q4], x[q4], y[q4], c);
+        for (int q4 = 0; q4 < 4; q4++) pointwise_digits<L, AX>(r[q4], x[q4], y[q4], c);
 #pragma unroll
         for (int q4 = 0; q4 < 4; q4++) lds_put<L>(lds, t.E, u * t.C + g + q4, r[q4]);
       } else {
@@ -553,7 +614,7 @@ __device__ __forceinline__ void pass_tile(u32* lds, const NttPassArgs& a, const 
         u32 y[L], r[L];
 #pragma unroll
         for (int j = 0; j < L; j++) y[j] = a.in2[(u64)j * n + src];
-        pointwise_digits<L, FW>(r, x, y, c);
+        pointwise_digits<L, AX>(r, x, y, c);
         lds_put<L>(lds, t.E, u * t.C + g, r);
       } else {
         lds_put<L>(lds, t.E, u * t.C + g, x);
@@ -565,15 +626,35 @@ __device__ __forceinline__ void pass_tile(u32* lds, const NttPassArgs& a, const 
   // ---- stages, R at a time in registers
   // later passes with 16+ columns store from the last round's registers
   const bool fuse = kFuseStore<L, FW> && t.K > 0 && t.C >= 16;
+  // bounds of the values in 64ths of q (OFF): a pass starts from [0, 16q)
+  // (the first from [0, q), and its first round of r stages ends below 2r q)
+  u32 lo = 0, hi = 16 * 64;
+  auto advance = [&](u32 stages, bool first) {
+    if (AX != kArithOffset) return false;
+    if (first) {
+      hi = 2 * 64 * stages;
+      return false;
+    }
+    const u32 move = stages * growth_64th<L>;
+    const bool red = lo < move || hi + move > 16 * 64;
+    if (red) {
+      lo = kOffset * 64;
+      hi = kOffset * 64 + 64 + 1;
+    }
+    lo -= move;
+    hi += move;
+    return red;
+  };
   u32 sg = 0;
   while (sg < t.k) {
     u32 rem = t.k - sg;
     if constexpr (LASTX && !MUL) {
       if (direct && sg == 0) {
+        const bool red = advance(R, t.K == 0);
         if (t.K == 0)
-          ntt_round<L, R, true, false, true>(lds, t, 0, a, c);
+          ntt_round<L, R, true, false, true, AX>(lds, t, 0, a, c, false);
         else
-          ntt_round<L, R, false, false, true>(lds, t, 0, a, c);
+          ntt_round<L, R, false, false, true, AX>(lds, t, 0, a, c, red);
         sg = R;
         __syncthreads();
         continue;
@@ -583,27 +664,29 @@ __device__ __forceinline__ void pass_tile(u32* lds, const NttPassArgs& a, const 
       // the last R + 1 stages with a cross-lane exchange before the last one
       if (rem == (u32)R + 1 && (t.logc == 4 || t.logc == 5) && ((t.E >> R) & 63u) == 0 &&
           (t.E >> R) >= blockDim.x && !(t.K == 0 && sg == 0)) {
+        const bool red = advance(R + 1, false);
         if constexpr (kFuseStore<L>) {
           if (fuse) {
-            ntt_round_last<L, R, true>(lds, t, sg, a, c);
+            ntt_round_last<L, R, true, AX>(lds, t, sg, a, c, red);
             return;
           }
         }
-        ntt_round_last<L, R, false>(lds, t, sg, a, c);
+        ntt_round_last<L, R, false, AX>(lds, t, sg, a, c, red);
         __syncthreads();
         break;
       }
     }
     const u32 rr = rem < (u32)R ? rem : (u32)R;
     const bool store = fuse && sg + rr == t.k;
+    const bool red = advance(rr, t.K == 0 && sg == 0);
     if (rr == 4) {
-      round_at<L, (R >= 4 ? 4 : 1), AR>(lds, t, sg, a, c, store);
+      round_at<L, (R >= 4 ? 4 : 1), AX>(lds, t, sg, a, c, store, red);
     } else if (rr == 3) {
-      round_at<L, (R >= 3 ? 3 : 1), AR>(lds, t, sg, a, c, store);
+      round_at<L, (R >= 3 ? 3 : 1), AX>(lds, t, sg, a, c, store, red);
     } else if (rr == 2) {
-      round_at<L, (R >= 2 ? 2 : 1), AR>(lds, t, sg, a, c, store);
+      round_at<L, (R >= 2 ? 2 : 1), AX>(lds, t, sg, a, c, store, red);
     } else {
-      round_at<L, 1, AR>(lds, t, sg, a, c, store);
+      round_at<L, 1, AX>(lds, t, sg, a, c, store, red);
     }
     sg += rr;
     if (!store) __syncthreads();
@@ -626,7 +709,7 @@ __device__ __forceinline__ void pass_tile(u32* lds, const NttPassArgs& a, const 
       u32 x[4][L];
 #pragma unroll
       for (int q4 = 0; q4 < 4; q4++) lds_get<L>(x[q4], lds, t.E, u * t.C + g + q4);
-      finish_elems<L, FW, 4>(x, a, c);
+      finish_elems<L, AX, 4>(x, a, c);
 #pragma unroll
       for (int j = 0; j < L; j++)
         *reinterpret_cast<uint4*>(a.out + (u64)j * n + dst) = make_uint4(x[0][j], x[1][j], x[2][j], x[3][j]);
@@ -640,7 +723,7 @@ __device__ __forceinline__ void pass_tile(u32* lds, const NttPassArgs& a, const 
       u32 x[4][L];
 #pragma unroll
       for (int q4 = 0; q4 < 4; q4++) lds_get<L>(x[q4], lds, t.E, rev_bits(v + q4, t.k) * t.C + g);
-      finish_elems<L, FW, 4>(x, a, c);
+      finish_elems<L, AX, 4>(x, a, c);
 #pragma unroll
       for (int j = 0; j < L; j++)
         *reinterpret_cast<uint4*>(a.out + (u64)j * n + dst) = make_uint4(x[0][j], x[1][j], x[2][j], x[3][j]);
@@ -662,7 +745,7 @@ __device__ __forceinline__ void pass_tile(u32* lds, const NttPassArgs& a, const 
       }
       u32 x[L];
       lds_get<L>(x, lds, t.E, u * t.C + g);
-      finish_elems<L, FW, 1>(&x, a, c);
+      finish_elems<L, AX, 1>(&x, a, c);
 #pragma unroll
       for (int j = 0; j < L; j++) a.out[(u64)j * n + dst] = x[j];
     }
@@ -805,6 +888,11 @@ inline NttC<L, FW> make_consts(const FieldRaw& f, const DigitConsts& dc) {
     u64 d = ((u64)f.q[j] << 1) + carry;  // 2q limb by limb (wraps for a full-width q, where it is unused)
     c.q2[j] = (u32)d;
     carry = d >> 32;
+  }
+  if constexpr (!FW && (offset_applies(L, 1) || offset_applies(L, 2))) {
+    for (int j = 0; j < L; j++) c.qsw[j] = f.qsw[j];
+    c.d = f.d;
+    c.cinv = f.cinv;
   }
   c.qinv = f.qinv;
   return c;

@@ -27,10 +27,8 @@
  *   leaves headroom for lazy reduction and Barrett's pre-scaled modulus; a
  *   modulus within 4 bits of the storage width ("full width", up to 1024
  *   bits in 32 limbs) computes in the same limbs with canonical operands and
- *   Montgomery products that carry out of the top limb (Section 5.2 names
- *   Montgomery multiplication for such moduli): vmul then takes two
- *   Montgomery products (the product variant does not apply), and the
- *   transforms use radix-2 and radix-4 units only;
+ *   products that may carry out of the top limb: vmul's product variant does
+ *   not apply then, and the transforms use radix-2 and radix-4 units only;
  *   n a power of two, 2 <= n <= 2^26 (BLAS: any n >= 0);
  *   omega of multiplicative order exactly n (omega^{n/2} == q - 1), which
  *   also implies n | q - 1 for prime q.  Primality of q is the caller's
@@ -120,7 +118,7 @@ int moma_unpack_planar(uint32_t limbs, uint64_t n, const uint32_t* d_planar, uin
  *   moma_vadd: out_i = (a_i + b_i) mod q
  *   moma_vsub: out_i = (a_i - b_i) mod q
  *   moma_vmul: out_i = (a_i * b_i) mod q      (Barrett reduction, Eq. (barrett))
- *   moma_axpy: out_i = (alpha * x_i + y_i) mod q   (Montgomery multiply by alpha)
+ *   moma_axpy: out_i = (alpha * x_i + y_i) mod q   (alpha kept with its quotient)
  * n is the element count (0 is a no-op).  Device arrays are limb-planar with
  * `limbs` planes of n words.  alpha is a host scalar in [0, q).
  */

@@ -166,6 +166,20 @@ static int batch_create(const moma_ntt_job_t* jobs, uint32_t njobs, BatchImpl& b
     std::vector<uint2> items;
   };
   std::map<std::tuple<int, int, uint32_t, bool>, BGroup> bgroups;
+  // Waves of radix-2 units of one pass, per compute limb count (each limb count
+  // is a chain of launches of its own): below four for every SIMD of the chip the
+  // chain is sparse, and its small jobs take shapes for the shortest way through
+  // their passes (batch_schedule, where both sides are measured).
+  constexpr uint64_t kSparseWaves = 4 * 1024;
+  constexpr uint64_t kSmallJob = 1ull << 18;
+  std::map<int, uint64_t> waves;
+  for (uint32_t j = 0; j < njobs; j++) {
+    std::shared_ptr<FieldEntry> fe;
+    std::string keep = g_detail;
+    if (jobs[j].kind < MOMA_JOB_VADD && build_field(jobs[j].q, jobs[j].limbs, &fe) == MOMA_OK)
+      waves[fe->f.L] += jobs[j].n / 128 * (jobs[j].kind == MOMA_JOB_CYCLIC_MUL ? 2 : 1);
+    g_detail = keep;  // (a job that fails is reported in its turn below)
+  }
   // groups of large jobs: the phases [group_phase, group_phase + group_span)
   constexpr uint64_t kGroupMinJobBytes = 16ull << 20, kGroupBytes = 256ull << 20;
   uint32_t group_phase = 0, group_span = 0;
@@ -232,8 +246,8 @@ static int batch_create(const moma_ntt_job_t* jobs, uint32_t njobs, BatchImpl& b
     // fill the chip, so jobs up to 2^18 points take large tiles (fewer passes
     // and workgroups); larger jobs keep their schedule, which measured faster
     // for them (2^24 points, and 1024-bit moduli at 2^20).
-    if (p->n <= (1ull << 18)) {
-      NttSchedule ds = batch_schedule(f.L, p->logn);
+    if (p->n <= kSmallJob) {
+      NttSchedule ds = batch_schedule(f.L, p->logn, waves[f.L] <= kSparseWaves);
       std::vector<NttPass> dp;
       std::string keep = g_detail;
       if (plan_passes(f.L, p->logn, ds, &dp, f.fw) == MOMA_OK) {

@@ -72,7 +72,7 @@ int build_field(const uint32_t* q, uint32_t limbs, std::shared_ptr<FieldEntry>* 
   // compute limbs keep 4 bits of headroom for the lazy reductions and
   // Barrett's pre-scaled modulus; a modulus within 4 bits of the storage
   // width (full width) computes in the storage limbs with canonical operands
-  // and Montgomery products that carry out of the top limb
+  // and products that may carry out of the top limb
   f.L = (M + 4 + 31) / 32;
   f.fw = f.L > (int)limbs ? 1 : 0;
   if (f.fw) f.L = (int)limbs;
@@ -182,25 +182,18 @@ int plan_passes(int L, uint32_t logn, const NttSchedule& s, std::vector<NttPass>
   return MOMA_OK;
 }
 
-// First feasible of an ordered list of (tile_log, col_log), with the radix
-// and thread count filled in by rule: radix 4 up to max_limbs_radix4 limbs,
-// and enough threads to give each one or two units per round.  (From 11 limbs
-// a radix-4 unit holds the lane at 3 waves per SIMD, 2 from 13.  For a lone
-// transform the fixed rule stays at radix 2 there, and the tuner and the cost
-// model find where radix 4 pays.  Inside a batch, where other jobs fill the
-// chip, 12-limb jobs take radix 4: the 4096-job batch ran 6.78 ms against
-// 6.89 ms with radix 2.)
-constexpr int kRuleMaxLimbsRadix4 = 10, kBatchMaxLimbsRadix4 = 12;
+// First feasible of an ordered list of (tile_log, col_log), with the thread
+// count filled in by rule: one or two units per thread and round, at most
+// max_threads.
 static NttSchedule first_feasible(int L, uint32_t logn, const std::vector<std::pair<uint32_t, uint32_t>>& shapes,
-                                  int max_limbs_radix4 = kRuleMaxLimbsRadix4) {
-  uint32_t radix = std::min(L <= max_limbs_radix4 ? 2u : 1u, max_radix_log(L));
+                                  uint32_t radix, uint32_t max_threads) {
   std::string keep = g_detail;
   NttSchedule last{};
   for (auto tc : shapes) {
     NttSchedule s{tc.first, tc.second, 0, radix};
     uint32_t e = std::min(logn, s.tile_log);
     uint32_t units = 1u << (e > s.radix_log ? e - s.radix_log : 0);
-    uint32_t t = std::min(units > 256 ? 256u : units, ntt_max_threads(L, s.radix_log));
+    uint32_t t = std::min(std::min(units, max_threads), ntt_max_threads(L, s.radix_log));
     s.threads = t < 64 ? 64 : (t + 63) / 64 * 64;
     last = s;
     std::vector<NttPass> ps;
@@ -228,20 +221,34 @@ NttSchedule default_schedule(int L, uint32_t logn) {
   if (logn <= t64) shapes.push_back({logn, 0});
   for (uint32_t cl : {4u, 3u, 2u}) shapes.push_back({t32, cl});
   for (uint32_t cl : {4u, 3u, 2u, 1u}) shapes.push_back({t64, cl});
-  return first_feasible(L, logn, shapes);
+  return first_feasible(L, logn, shapes, std::min(L <= 10 ? 2u : 1u, max_radix_log(L)), 256);
 }
 
-// Shape for a small job inside a batch, where other jobs fill the chip: one
-// pass when the transform fits a 64 KiB tile, else the largest tiles (fewest
-// passes) with 32 or 16 columns.
-NttSchedule batch_schedule(int L, uint32_t logn) {
+// Shape for a small job inside a batch.
+// Where the batch's other jobs of this limb count fill the chip: one pass when
+// the transform fits a 64 KiB tile, else the largest tiles (fewest passes) with
+// 32 or 16 columns, in radix-4 units up to 8 limbs (64 transforms of 2^16
+// points: 352 bits 539 us with radix-2 units against 638, 384 bits 564 against 677;
+// 288 bits 382 against 394; but 256 bits 323 against 297).
+// `sparse`, where they do not (batch.cpp draws the line): 32 KiB tiles, radix-2
+// units and up to 512 threads, for the shortest way through each job's passes
+// (2 mixed jobs 80 -> 62 us, 16: 173 -> 132, 40: 233 -> 149, 100: 288 -> 207; 4
+// transforms of 2^16 points at 256 bits 56 -> 45 us; but 16 of them 96 -> 118).
+NttSchedule batch_schedule(int L, uint32_t logn, bool sparse) {
   uint32_t t64 = tile_log_for(16384u / (uint32_t)L), t32 = tile_log_for(8192u / (uint32_t)L);
+  if (sparse) {
+    std::vector<std::pair<uint32_t, uint32_t>> shapes;
+    if (logn <= t32) shapes.push_back({logn, 0});
+    for (uint32_t cl : {5u, 4u, 3u, 2u, 1u}) shapes.push_back({t32, cl});
+    for (uint32_t cl : {2u, 1u}) shapes.push_back({t64, cl});
+    return first_feasible(L, logn, shapes, 1, 512);
+  }
   std::vector<std::pair<uint32_t, uint32_t>> shapes;
   if (logn <= t64) shapes.push_back({logn, 0});
   for (uint32_t cl : {5u, 4u}) shapes.push_back({t64, cl});
   for (uint32_t cl : {5u, 4u, 3u, 2u}) shapes.push_back({t32, cl});
   for (uint32_t cl : {3u, 2u, 1u}) shapes.push_back({t64, cl});
-  return first_feasible(L, logn, shapes, kBatchMaxLimbsRadix4);
+  return first_feasible(L, logn, shapes, std::min(L <= 8 ? 2u : 1u, max_radix_log(L)), 256);
 }
 
 NttSchedule initial_schedule(int L, uint32_t logn, bool fw) {

@@ -1,5 +1,5 @@
 // hostbig.hpp - the library's host-side big integers, used once per plan to
-// derive constants (Montgomery -q^-1 mod 2^32, R mod q, R^2 mod q, Barrett mu,
+// derive constants (Montgomery -q^-1 mod 2^32, R mod q, Barrett mu,
 // omega^-1, n^-1, twiddle ladders).  Not on the hot path: simple shift-subtract
 // division and square-and-multiply are enough.
 #pragma once

@@ -229,6 +229,9 @@ def main():
     t.add_argument("--db", nargs="+", required=True)
     t.add_argument("--model", required=True)
     t.add_argument("--epochs", type=int, default=300)
+    t.add_argument("--batch", type=int, default=256)
+    t.add_argument("--lr", type=float, default=3e-3)
+    t.add_argument("--seed", type=int, default=7)
     p = sub.add_parser("picks")
     p.add_argument("--db", nargs="+", required=True)
     p.add_argument("--model", required=True)
@@ -239,7 +242,7 @@ def main():
     w.add_argument("--logn", default="12,16")
     a = ap.parse_args()
     if a.cmd == "train":
-        train_all(a.db, a.model, epochs=a.epochs)
+        train_all(a.db, a.model, seed=a.seed, epochs=a.epochs, batch=a.batch, lr=a.lr)
     elif a.cmd == "picks":
         picks(a.db, a.model, a.out)
     elif a.cmd == "widths":

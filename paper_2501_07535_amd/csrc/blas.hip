@@ -12,29 +12,47 @@
 
 namespace moma {
 
-template <int L, bool FW>
-struct BlasC {
-  u32 q[L];
+// constants of the multiplies: in digits, or (WORDS) on words
+template <int L, bool FW, bool WORDS = (L <= kWordLimbs)>
+struct MulC {
   u32 nqd[Digits<L, FW>::D];
   u32 alpha_d[Digits<L, FW>::D];
   u32 alpha_q[Digits<L, FW>::D];
   BarrettC<L, FW> bc;
-  BarrettKaraC<L> kc;
+};
+template <int L, bool FW>
+struct MulC<L, FW, true> {
+  u32 qinv;
+  u32 r2[L];       // 2^(64L) mod q (full-width vmul)
+  u32 alpha_m[L];  // alpha 2^(32L) mod q
 };
 
-// One element's operation.  A full-width modulus (FW) differs only where a sum
-// or a product below 2q can carry out of the top limb.
+template <int L, bool FW>
+struct BlasC : MulC<L, FW> {
+  u32 q[L];
+  BarrettWordC<L> kc;
+};
+
+// One element's operation.  A full-width modulus (FW) differs where a sum or a
+// product below 2q can carry out of the top limb, and in vmul on words: it has no
+// headroom for Barrett's pre-scaled modulus and takes two Montgomery products,
+// (a b 2^(-32L)) 2^(64L) 2^(-32L).
 template <int L, int OP, bool KARA, bool FW>
 __device__ __forceinline__ void blas_elem(u32* r, const u32* a, const u32* b, const BlasC<L, FW>& c) {
   if constexpr (OP == OP_VMUL) {
-    if constexpr (KARA)
-      barrett_mul_kara<L>(r, a, b, c.kc);
-    else
+    if constexpr (KARA || (L <= kWordLimbsVmul && !FW)) {
+      barrett_mul_words<L, KARA>(r, a, b, c.kc);
+    } else if constexpr (L <= kWordLimbs) {
+      u32 t[L], r2v[L], qv[L];
+      to_vgprs<L>(qv, c.q);
+      to_vgprs<L>(r2v, c.r2);
+      mont_mul_fw<L>(t, a, b, c.q, c.qinv, qv);
+      mont_mul_fw<L>(r, t, r2v, c.q, c.qinv, qv);
+    } else {
       barrett_mul_digits<L, FW>(r, a, b, c.bc);
+    }
     return;
   }
-  u32 t[L], x[L], top = 0;
-  if constexpr (OP == OP_AXPY) quot_mul<L, FW>(t, a, c.alpha_d, c.alpha_q, c.nqd, &top);  // alpha x in [0, 2q)
   if constexpr (FW) {
     u32 qv[L];
     to_vgprs<L>(qv, c.q);
@@ -43,7 +61,16 @@ __device__ __forceinline__ void blas_elem(u32* r, const u32* a, const u32* b, co
     } else if constexpr (OP == OP_VSUB) {
       mod_sub_v<L>(r, a, b, qv);
     } else {
-      reduce_top<L>(x, t, top, qv);
+      u32 x[L];
+      if constexpr (L <= kWordLimbs) {
+        u32 av[L];
+        to_vgprs<L>(av, c.alpha_m);
+        mont_mul_fw<L>(x, a, av, c.q, c.qinv, qv);  // alpha x
+      } else {
+        u32 t[L], top = 0;
+        quot_mul<L, FW>(t, a, c.alpha_d, c.alpha_q, c.nqd, &top);  // alpha x in [0, 2q)
+        reduce_top<L>(x, t, top, qv);
+      }
       mod_add_fw<L>(r, x, b, qv);
     }
   } else {
@@ -52,7 +79,14 @@ __device__ __forceinline__ void blas_elem(u32* r, const u32* a, const u32* b, co
     } else if constexpr (OP == OP_VSUB) {
       mod_sub<L>(r, a, b, c.q);
     } else {
-      reduce_once<L>(x, t, c.q);
+      u32 x[L];
+      if constexpr (L <= kWordLimbs) {
+        mont_mul<L>(x, a, c.alpha_m, c.q, c.qinv);
+      } else {
+        u32 t[L];
+        quot_mul<L>(t, a, c.alpha_d, c.alpha_q, c.nqd);
+        reduce_once<L>(x, t, c.q);
+      }
       mod_add<L>(r, x, b, c.q);
     }
   }
@@ -93,18 +127,27 @@ static BlasC<L, FW> blas_consts(const FieldRaw& f, const BlasArgs& a) {
   memset(&c, 0, sizeof(c));
   for (int j = 0; j < L; j++) {
     c.q[j] = f.q[j];
-    c.bc.qs[j] = f.vd && j ? f.q[j] << f.vd | f.q[j - 1] >> (32 - f.vd) : f.q[j] << f.vd;
     c.kc.qn[j] = f.qn[j];
     c.kc.mu[j] = f.mu[j];
   }
-  for (int j = 0; j < Digits<L, FW>::D; j++) {
-    c.nqd[j] = f.nqd[j];
-    c.alpha_d[j] = a.alpha_d[j];
-    c.alpha_q[j] = a.alpha_q[j];
-    c.bc.mu[j] = f.vmu[j];
-    c.bc.nqn[j] = f.vnqn[j];
+  if constexpr (L <= kWordLimbs) {
+    for (int j = 0; j < L; j++) {
+      c.r2[j] = f.r2[j];
+      c.alpha_m[j] = a.alpha_m[j];
+    }
+    c.qinv = f.qinv;
+  } else {
+    for (int j = 0; j < L; j++)
+      c.bc.qs[j] = f.vd && j ? f.q[j] << f.vd | f.q[j - 1] >> (32 - f.vd) : f.q[j] << f.vd;
+    for (int j = 0; j < Digits<L, FW>::D; j++) {
+      c.nqd[j] = f.nqd[j];
+      c.alpha_d[j] = a.alpha_d[j];
+      c.alpha_q[j] = a.alpha_q[j];
+      c.bc.mu[j] = f.vmu[j];
+      c.bc.nqn[j] = f.vnqn[j];
+    }
+    c.bc.d = f.vd;
   }
-  c.bc.d = f.vd;
   c.kc.d = f.d;
   return c;
 }

@@ -81,6 +81,7 @@ int build_field(const uint32_t* q, uint32_t limbs, std::shared_ptr<FieldEntry>* 
   f.qinv = neg_inv32(f.q[0]);
   HBig one_m = HBig::mod(HBig::pow2(32 * f.L), Q);
   one_m.to_limbs(f.one_m, kMaxLimbs);
+  if (f.L <= kWordLimbs) HBig::mod(HBig::pow2(64 * f.L), Q).to_limbs(f.r2, kMaxLimbs);
   if (!f.fw) {
     int Mn = 32 * f.L - 4;
     f.d = (uint32_t)(Mn - M);
@@ -607,13 +608,19 @@ int axpy_alpha(FieldEntry& fe, const uint32_t* alpha, uint32_t limbs, BlasArgs* 
   std::vector<uint32_t> key(alpha, alpha + limbs);
   std::lock_guard<std::mutex> lk(g_mu);
   if (fe.alpha_key != key) {
-    HBig A = HBig::from_limbs(alpha, (int)limbs), aq;
+    HBig A = HBig::from_limbs(alpha, (int)limbs);
     if (HBig::cmp(A, fe.Q) >= 0) return set_error(MOMA_E_ARG, "alpha must be < q");
-    HBig::divmod(HBig::shl(A, digit_bits(fe.f.L) * digit_count(fe.f.L, fe.f.fw)), fe.Q, &aq, nullptr);
-    digits_of(A, fe.f.L, fe.f.fw, fe.alpha_d);
-    digits_of(aq, fe.f.L, fe.f.fw, fe.alpha_q);
+    if (fe.f.L <= kWordLimbs) {
+      HBig::mulmod(A, fe.one_m, fe.Q).to_limbs(fe.alpha_m, kMaxLimbs);
+    } else {
+      HBig aq;
+      HBig::divmod(HBig::shl(A, digit_bits(fe.f.L) * digit_count(fe.f.L, fe.f.fw)), fe.Q, &aq, nullptr);
+      digits_of(A, fe.f.L, fe.f.fw, fe.alpha_d);
+      digits_of(aq, fe.f.L, fe.f.fw, fe.alpha_q);
+    }
     fe.alpha_key = key;
   }
+  memcpy(a->alpha_m, fe.alpha_m, sizeof(fe.alpha_m));
   memcpy(a->alpha_d, fe.alpha_d, sizeof(fe.alpha_d));
   memcpy(a->alpha_q, fe.alpha_q, sizeof(fe.alpha_q));
   return MOMA_OK;

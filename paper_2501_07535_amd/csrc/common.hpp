@@ -25,6 +25,16 @@ constexpr int digit_count(int L, bool fw = false) {
 constexpr int barrett_off(int L, bool fw = false) {
   return digit_bits(L) * digit_count(L, fw) - 1 - (fw ? 32 * L : 32 * L - 4);
 }
+// Widest limb counts whose elementwise multiplies stay on 32-bit words (vmul of
+// moduli with headroom; axpy and full-width vmul): D digits take 2D^2 + 2D
+// products (vmul) or about 3/2 D^2 (axpy), and with 3 to 5 of them that is more
+// instructions than 2 to 4 words need, for which these calls, bound by memory,
+// have little room.  2^24 elements, digits and words: vmul at 64 bits 70.6 and
+// 66.5 us, 96 bits 95.5 and 93.2, 128 bits 125.5 and 124.0 (160 bits 162.9 and
+// 161.7, but 2^20 of 256 bits 21.2 and 22.3); axpy at 64 bits 68.6 and 67.9, 96
+// bits 96.4 and 94.0, 128 bits 127.0 and 127.2; full-width vmul at 64 bits 71.0
+// and 67.0, 96 bits 97.4 and 95.9, 128 bits 126.3 and 127.0.
+constexpr int kWordLimbsVmul = 4, kWordLimbs = 3;
 // words of one twiddle table entry: the quotient's digits, the twiddle's
 // digits, padded to whole 16-byte loads
 constexpr int tw_words(int L, bool fw = false) { return (2 * digit_count(L, fw) + 3) / 4 * 4; }
@@ -60,6 +70,7 @@ struct FieldRaw {
   uint32_t nqd[40];        // 2^(bD) - q in digits
   uint32_t qsw[kMaxLimbs]; // q in signed words: the sum of (int32) qsw[i] 2^(32 i)
   uint32_t cinv;           // floor(2^58 / (qt + 1)), qt the top 32 bits of q 2^d (2^27 <= qt < 2^28)
+  uint32_t r2[kMaxLimbs];  // 2^(64L) mod q (full-width vmul on words)
 };
 
 enum BlasOp { OP_VADD = 0, OP_VSUB = 1, OP_VMUL = 2, OP_AXPY = 3 };
@@ -69,7 +80,8 @@ struct BlasArgs {
   const uint32_t* b;
   uint32_t* out;
   uint64_t n;
-  uint32_t alpha_d[40];  // axpy: alpha in digits
+  uint32_t alpha_m[kMaxLimbs];  // axpy: alpha 2^(32L) mod q (the word form)
+  uint32_t alpha_d[40];  // alpha in digits
   uint32_t alpha_q[40];  // and its quotient floor(alpha 2^(bD) / q)
   uint32_t variant;      // vmul: 0 schoolbook products, 1 Karatsuba (L >= 2)
   uint32_t ls;           // storage planes (>= L; the planes above L are written as zero)

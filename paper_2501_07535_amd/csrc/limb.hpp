@@ -741,8 +741,9 @@ __device__ __forceinline__ void ct_fw_tail(u32* x, u32* y, const u32* t, u32 top
 // and up (those below weigh less than 2^-b D of m's unit) and the last one mod
 // B^D: 2D^2 + 2D products, one v_mad_u64_u32 each, where the same method on
 // 32-bit words took 2.5 L^2 products of two instructions.
-// Bound by the issue of those products from 12 limbs on (below, by memory):
-// 2^24 products at 768 bits took 1534 us in words, 1202 us so.
+// Bound by the issue of those products from 12 limbs on, by memory below:
+// 2^24 products at 768 bits took 1534 us in words, 1202 us so.  (Up to 4 limbs the
+// digits are more instructions than the words: kWordLimbsVmul.)
 // m is floor(P / qn) or one less: what P loses below B^(D-1) and mu below 1
 // takes off less than 2^(2-b) and 2^(W0 - bD) <= 1/2 of m's unit.
 template <int L, bool FW = false>
@@ -819,12 +820,12 @@ __device__ __forceinline__ void barrett_mul_digits(u32* r, const u32* a, const u
   }
 }
 
-// Constants of the Karatsuba variant, on 32-bit words, following Listings 1 and
-// 4 generalised to L limbs.  The modulus is pre-scaled to qn = q * 2^d with bitlen(qn) = M = 32L-4,
+// Constants of the form on 32-bit words, following Listings 1 and 4 generalised
+// to L limbs.  The modulus is pre-scaled to qn = q * 2^d with bitlen(qn) = M = 32L-4,
 // so the paper's shifts by M-2 and M+5 fall at fixed limb/bit positions:
 // mu = floor(2^(2M+3) / qn) < 2^(M+4) = 2^(32L).
 template <int L>
-struct BarrettKaraC {
+struct BarrettWordC {
   u32 qn[L];
   u32 mu[L];
   u32 d;
@@ -902,9 +903,10 @@ __device__ __forceinline__ void kara_mul(u32* t, const u32* a, const u32* b) {
 //   a' = a*2^d, t = a'*b < qn^2, r1 = t >> (M-2), r2 = (r1*mu) >> (M+5),
 //   t - r2*qn in [0, 2qn) (one correction), result = (that mod qn) >> d.
 // The subtraction uses only the low L limbs, as in _dmulmod: the difference
-// fits in L limbs.  The two full products (a*b, r1*mu) by one level of Karatsuba.
-template <int L>
-__device__ __forceinline__ void barrett_mul_kara(u32* r, const u32* a, const u32* b, const BarrettKaraC<L>& c) {
+// fits in L limbs.  KARA: the two full products (a*b, r1*mu) by one level of
+// Karatsuba.
+template <int L, bool KARA>
+__device__ __forceinline__ void barrett_mul_words(u32* r, const u32* a, const u32* b, const BarrettWordC<L>& c) {
   // a' = a << d (a < q so a' < qn < 2^(32L-4): no overflow past L limbs)
   u32 as[L];
   if (c.d == 0) {
@@ -917,16 +919,42 @@ __device__ __forceinline__ void barrett_mul_kara(u32* r, const u32* a, const u32
   }
   // t = a' * b, 2L limbs
   u32 t[2 * L];
-  kara_mul<L>(t, as, b);
+  if constexpr (KARA) {
+    kara_mul<L>(t, as, b);
+  } else {
+    u64 acc = 0;
+    u32 hi = 0;
+#pragma unroll
+    for (int k = 0; k < 2 * L - 1; k++) {
+#pragma unroll
+      for (int i = (k < L ? 0 : k - L + 1); i <= (k < L ? k : L - 1); i++) mac_vv(acc, hi, as[i], b[k - i]);
+      t[k] = (u32)acc;
+      shift_col(acc, hi);
+    }
+    t[2 * L - 1] = (u32)acc;
+  }
   // r1 = t >> (M - 2) = t >> (32(L-1) + 26): limbs L-1 .. 2L-1, bit offset 26
   u32 r1[L];
 #pragma unroll
   for (int i = 0; i < L; i++) r1[i] = __builtin_amdgcn_alignbit(t[L + i], t[L - 1 + i], 26);
   // r2 = (r1 * mu) >> (M + 5) = >> (32L + 1): need product limbs L .. 2L-1 exactly
   u32 p[2 * L];
-  u32 muv[L];
-  to_vgprs<L>(muv, c.mu);
-  kara_mul<L>(p, r1, muv);
+  if constexpr (KARA) {
+    u32 muv[L];
+    to_vgprs<L>(muv, c.mu);
+    kara_mul<L>(p, r1, muv);
+  } else {
+    u64 acc = 0;
+    u32 hi = 0;
+#pragma unroll
+    for (int k = 0; k < 2 * L - 1; k++) {
+#pragma unroll
+      for (int i = (k < L ? 0 : k - L + 1); i <= (k < L ? k : L - 1); i++) mac_vs(acc, hi, r1[i], c.mu[k - i]);
+      p[k] = (u32)acc;
+      shift_col(acc, hi);
+    }
+    p[2 * L - 1] = (u32)acc;
+  }
   u32 r2[L];
 #pragma unroll
   for (int i = 0; i < L - 1; i++) r2[i] = __builtin_amdgcn_alignbit(p[L + i + 1], p[L + i], 1);

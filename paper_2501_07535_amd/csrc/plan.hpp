@@ -18,8 +18,9 @@ struct FieldEntry {
   DigitConsts dc;
   HBig Q, one_m;
   HBig adj;  // 2^(bD) mod q: R of the digit form
-  // last axpy scalar, cached with its digits and its quotient's
+  // last axpy scalar, cached with its Montgomery form, its digits and its quotient's
   std::vector<uint32_t> alpha_key;
+  uint32_t alpha_m[kMaxLimbs] = {0};
   uint32_t alpha_d[40] = {0};
   uint32_t alpha_q[40] = {0};
 };
@@ -89,7 +90,7 @@ int launch_blas_batch(int op, int L, uint32_t variant, bool fw, const void* recs
                       const uint2* items, uint32_t nitems, hipStream_t s);
 // vmul's product variant for a compute limb count (capi.cpp)
 uint32_t vmul_variant(int L);
-// alpha (storage limbs words), validated < q, as axpy's digits and quotient in *a
+// alpha (storage limbs words), validated < q, in axpy's forms in *a
 int axpy_alpha(FieldEntry& fe, const uint32_t* alpha, uint32_t limbs, BlasArgs* a);
 // n pseudo-random residues below q in Ls = f.Ls storage planes (timing inputs for the tuners)
 int fill_random_residues(const FieldRaw& f, uint32_t* d, uint64_t n, uint32_t seed, hipStream_t s);

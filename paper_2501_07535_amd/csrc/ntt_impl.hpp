@@ -759,8 +759,9 @@ struct PassTraits {
   static constexpr int live = L << R;
   static constexpr int max_threads = live <= 16 ? 1024 : (live <= 32 ? 512 : 256);
   // radix-4 units of 7 or 8 limbs need just over the 128 registers that four
-  // waves per SIMD leave a lane
-  static constexpr int min_waves = R == 2 && live > 24 && live <= 32 ? 4 : 1;
+  // waves per SIMD leave a lane; full-width radix-2 units of 32 limbs just over
+  // the 256 of two (2^16 points 199 us with one wave, 139 with two)
+  static constexpr int min_waves = R == 2 && live > 24 && live <= 32 ? 4 : (R == 1 && L == 32 ? 2 : 1);
 };
 
 // One pass of one transform: one tile per workgroup.

@@ -40,9 +40,7 @@ struct BatchLaunch {
   bool mul, variant, fw;
   uint32_t phase, radix_log, threads, grid, nitems;
   size_t lds;
-  const NttPassArgs* d_passes;
-  const void* d_consts;
-  const uint2* d_items;
+  size_t passes, consts, items;  // places in the batch's tables
 };
 
 struct ZeroFill {
@@ -55,9 +53,7 @@ struct BlasLaunch {
   int op, L;
   bool fw;
   uint32_t variant, nitems;
-  const void* d_recs;
-  const void* d_consts;
-  const uint2* d_items;
+  size_t recs, consts, items;  // places in the batch's tables
 };
 
 struct BatchImpl {
@@ -90,14 +86,18 @@ struct BatchImpl {
   }
 };
 
-static int dev_upload(BatchImpl& b, const void* host, size_t bytes, void** out) {
-  void* d = nullptr;
-  if (hipMalloc(&d, bytes ? bytes : 4)) return set_error(MOMA_E_NOMEM, "batch table allocation failed");
-  b.dev_allocs.push_back(d);
-  if (bytes && hipMemcpy(d, host, bytes, hipMemcpyHostToDevice)) return hip_fail(1, "batch table upload");
-  *out = d;
-  return MOMA_OK;
-}
+// The launches' tables (records, constants, items), laid out on the host and
+// uploaded in one piece: an allocation and a copy for each cost more than
+// everything else in the creation of a small batch.
+struct Tables {
+  std::vector<uint8_t> bytes;
+  size_t add(const void* host, size_t n) {
+    const size_t at = (bytes.size() + 255) / 256 * 256;
+    bytes.resize(at + n);
+    if (n) memcpy(bytes.data() + at, host, n);
+    return at;
+  }
+};
 
 static int batch_create(const moma_ntt_job_t* jobs, uint32_t njobs, BatchImpl& b) {
   if (!jobs && njobs) return set_error(MOMA_E_ARG, "jobs is NULL");
@@ -301,18 +301,15 @@ static int batch_create(const moma_ntt_job_t* jobs, uint32_t njobs, BatchImpl& b
         first_out, job.d_out, ph0);
     if (f.Ls > f.L && job.d_out != job.d_in) b.fills.push_back({job.d_out, p->n, f.L, f.Ls});
   }
-  // upload tables and build the launch list, phase by phase
+  // lay out the tables and build the launch list, phase by phase
+  Tables tables;
   uint32_t max_phase = 0;
   for (auto& kv : groups)
     for (auto& it : kv.second.items) max_phase = std::max(max_phase, it.first + 1);
-  std::map<GKey, std::pair<void*, void*>> dev_recs;
+  std::map<GKey, std::pair<size_t, size_t>> group_tables;
   for (auto& kv : groups) {
-    void *dp = nullptr, *dc = nullptr;
-    int rc = dev_upload(b, kv.second.recs.data(), kv.second.recs.size() * sizeof(NttPassArgs), &dp);
-    if (rc) return rc;
-    rc = dev_upload(b, kv.second.consts.data(), kv.second.consts.size(), &dc);
-    if (rc) return rc;
-    dev_recs[kv.first] = {dp, dc};
+    const size_t recs = tables.add(kv.second.recs.data(), kv.second.recs.size() * sizeof(NttPassArgs));
+    group_tables[kv.first] = {recs, tables.add(kv.second.consts.data(), kv.second.consts.size())};
   }
   for (uint32_t ph = 0; ph < max_phase; ph++) {
     for (auto& kv : groups) {
@@ -323,9 +320,6 @@ static int batch_create(const moma_ntt_job_t* jobs, uint32_t njobs, BatchImpl& b
       std::stable_sort(v.begin(), v.end(), [](const auto& x, const auto& y) { return x.first > y.first; });
       std::vector<uint2> items(v.size());
       for (size_t i = 0; i < v.size(); i++) items[i] = v[i].second;
-      void* di = nullptr;
-      int rc = dev_upload(b, items.data(), items.size() * sizeof(uint2), &di);
-      if (rc) return rc;
       BatchLaunch bl;
       bl.L = L;
       bl.phase = ph;
@@ -338,9 +332,9 @@ static int batch_create(const moma_ntt_job_t* jobs, uint32_t njobs, BatchImpl& b
       bl.nitems = (uint32_t)items.size();
       if (items.size() > 0x7fffffffull) return set_error(MOMA_E_UNSUPPORTED, "batch phase has too many tiles");
       bl.grid = bl.nitems;  // one workgroup per item
-      bl.d_passes = (const NttPassArgs*)dev_recs[kv.first].first;
-      bl.d_consts = dev_recs[kv.first].second;
-      bl.d_items = (const uint2*)di;
+      bl.passes = group_tables[kv.first].first;
+      bl.consts = group_tables[kv.first].second;
+      bl.items = tables.add(items.data(), items.size() * sizeof(uint2));
       b.launches.push_back(bl);
       b.items += bl.nitems;
     }
@@ -353,16 +347,18 @@ static int batch_create(const moma_ntt_job_t* jobs, uint32_t njobs, BatchImpl& b
     bl.variant = std::get<2>(kv.first);
     bl.fw = std::get<3>(kv.first);
     bl.nitems = (uint32_t)g.items.size();
-    void *dr = nullptr, *dc = nullptr, *di = nullptr;
-    int rc = dev_upload(b, g.recs.data(), g.recs.size() * sizeof(BlasJobRec), &dr);
-    if (!rc) rc = dev_upload(b, g.consts.data(), g.consts.size(), &dc);
-    if (!rc) rc = dev_upload(b, g.items.data(), g.items.size() * sizeof(uint2), &di);
-    if (rc) return rc;
-    bl.d_recs = dr;
-    bl.d_consts = dc;
-    bl.d_items = (const uint2*)di;
+    bl.recs = tables.add(g.recs.data(), g.recs.size() * sizeof(BlasJobRec));
+    bl.consts = tables.add(g.consts.data(), g.consts.size());
+    bl.items = tables.add(g.items.data(), g.items.size() * sizeof(uint2));
     b.blas.push_back(bl);
     b.items += bl.nitems;
+  }
+  uint8_t* dev = nullptr;
+  if (!tables.bytes.empty()) {
+    if (hipMalloc((void**)&dev, tables.bytes.size())) return set_error(MOMA_E_NOMEM, "batch table allocation failed");
+    b.dev_allocs.push_back(dev);
+    if (hipMemcpy(dev, tables.bytes.data(), tables.bytes.size(), hipMemcpyHostToDevice))
+      return hip_fail(1, "batch table upload");
   }
   for (const BatchLaunch& bl : b.launches) ntt_batch_prepare(bl.L, bl.radix_log, bl.fw, bl.lds);
   // Capture the launches into one graph.  All passes of a job have the job's
@@ -393,7 +389,8 @@ static int batch_create(const moma_ntt_job_t* jobs, uint32_t njobs, BatchImpl& b
   if (hipStreamBeginCapture(b.cap, hipStreamCaptureModeThreadLocal)) return hip_fail(1, "begin capture");
   int err = 0;
   for (const BlasLaunch& bl : b.blas) {
-    err = launch_blas_batch(bl.op, bl.L, bl.variant, bl.fw, bl.d_recs, bl.d_consts, bl.d_items, bl.nitems, b.cap);
+    err = launch_blas_batch(bl.op, bl.L, bl.variant, bl.fw, dev + bl.recs, dev + bl.consts, (const uint2*)(dev + bl.items),
+                            bl.nitems, b.cap);
     if (err) break;
   }
   if (!err && !b.side.empty()) {
@@ -405,8 +402,9 @@ static int batch_create(const moma_ntt_job_t* jobs, uint32_t njobs, BatchImpl& b
   for (size_t k = 0; !err && k < b.launches.size(); k++) {
     const BatchLaunch& bl = b.launches[k];
     const size_t slot = slot_of[bl.L];
-    err = launch_ntt_batch(bl.L, bl.radix_log, bl.mul, bl.variant, bl.fw, bl.threads, bl.lds, bl.grid, bl.d_passes,
-                           bl.d_consts, bl.d_items, bl.nitems, slot ? b.side[slot - 1] : b.cap);
+    err = launch_ntt_batch(bl.L, bl.radix_log, bl.mul, bl.variant, bl.fw, bl.threads, bl.lds, bl.grid,
+                           (const NttPassArgs*)(dev + bl.passes), dev + bl.consts, (const uint2*)(dev + bl.items),
+                           bl.nitems, slot ? b.side[slot - 1] : b.cap);
   }
   for (size_t k = 0; !err && k < b.side.size(); k++) {
     hipEvent_t join = record(b.side[k]);

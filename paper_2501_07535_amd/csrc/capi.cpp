@@ -109,15 +109,17 @@ int build_field(const uint32_t* q, uint32_t limbs, std::shared_ptr<FieldEntry>* 
       }
       f.cinv = (uint32_t)((1ull << 58) / ((uint64_t)f.qn[f.L - 1] + 1));
     }
-    // vmul: the modulus scaled to bD - 1 bits
-    f.vd = (uint32_t)((f.fw ? 32 * f.L : 32 * f.L - 4) - M);
-    HBig qs = HBig::shl(Q, (int)f.vd + barrett_off(f.L, f.fw)), vmu;
-    digits_of(HBig::sub(HBig::pow2(b * D), qs), f.L, f.fw, f.vnqn);
-    HBig::divmod(HBig::pow2(2 * b * D), qs, &vmu, nullptr);
-    digits_of(vmu, f.L, f.fw, f.vmu);
-    uint32_t vtop[2] = {0, 0};
-    HBig::shr(vmu, b * (D - 1)).to_limbs(vtop, 2);
-    f.vmu[D - 1] = vtop[0];
+    // vmul in digits: the modulus scaled to bD - 1 bits
+    if (f.L > kWordLimbs) {
+      f.vd = (uint32_t)((f.fw ? 32 * f.L : 32 * f.L - 4) - M);
+      HBig qs = HBig::shl(Q, (int)f.vd + barrett_off(f.L, f.fw)), vmu;
+      digits_of(HBig::sub(HBig::pow2(b * D), qs), f.L, f.fw, f.vnqn);
+      HBig::divmod(HBig::pow2(2 * b * D), qs, &vmu, nullptr);
+      digits_of(vmu, f.L, f.fw, f.vmu);
+      uint32_t vtop[2] = {0, 0};
+      HBig::shr(vmu, b * (D - 1)).to_limbs(vtop, 2);
+      f.vmu[D - 1] = vtop[0];
+    }
     dc.qinvd = f.qinv & ((1u << b) - 1);
     fe->adj = HBig::mod(HBig::pow2(b * D), Q);
     fe->adj.to_limbs(dc.adj, kMaxLimbs);
@@ -287,19 +289,13 @@ static int upload(uint32_t** dptr, const std::vector<uint32_t>& host) {
   return e;
 }
 
-static void free_tables(DirTables* t) {
-  (void)hipFree(t->tw);
-  (void)hipFree(t->ladder);
-  t->tw = t->ladder = nullptr;
-}
+// Words of one direction's ladder, from which its twiddle table is made:
+// (logn + 2) x L, w^(2^b) in Montgomery form, then 1, then 2^(bD) mod q.
+static size_t ladder_words(const NttPlan& p) { return (size_t)(p.logn + 2) * p.fe->f.L; }
 
-// One direction's ladder and twiddle table.  On failure both are freed (and
-// NULL), so a failed plan build holds no device memory for this direction.
-static int build_tables(NttPlan& p, const HBig& w, DirTables* t) {
-  const FieldRaw& f = p.fe->f;
+static void fill_ladder(const NttPlan& p, const HBig& w, uint32_t* lad) {
   const HBig& Q = p.fe->Q;
-  int L = f.L;
-  std::vector<uint32_t> lad((size_t)(p.logn + 2) * L);
+  int L = p.fe->f.L;
   HBig cur = w;
   for (uint32_t b = 0; b < p.logn; b++) {
     HBig m = HBig::mulmod(cur, p.fe->one_m, Q);
@@ -308,20 +304,17 @@ static int build_tables(NttPlan& p, const HBig& w, DirTables* t) {
   }
   p.fe->one_m.to_limbs(&lad[(size_t)p.logn * L], L);
   for (int j = 0; j < L; j++) lad[(size_t)(p.logn + 1) * L + j] = p.fe->dc.adj[j];
-  int e = upload(&t->ladder, lad);
-  if (e) return hip_fail(e, "ladder upload");
-  e = (int)hipMalloc((void**)&t->tw, (size_t)p.n * tw_words(L, f.fw) * sizeof(uint32_t));
-  if (e) {
+}
+
+// One direction's twiddle table, from its ladder on the device.
+static int build_table(NttPlan& p, const uint32_t* ladder, DirTables* t) {
+  const FieldRaw& f = p.fe->f;
+  if (hipMalloc((void**)&t->tw, (size_t)p.n * tw_words(f.L, f.fw) * sizeof(uint32_t))) {
     t->tw = nullptr;
-    free_tables(t);
     return set_error(MOMA_E_NOMEM, "twiddle table allocation failed");
   }
-  e = launch_twiddle_gen(f, p.fe->dc, t->tw, p.n, p.logn, t->ladder, 0);
-  if (e) {
-    free_tables(t);
-    return hip_fail(e, "twiddle generation launch");
-  }
-  return MOMA_OK;
+  int e = launch_twiddle_gen(f, p.fe->dc, t->tw, p.n, p.logn, ladder, 0);
+  return e ? hip_fail(e, "twiddle generation launch") : MOMA_OK;
 }
 
 static std::vector<uint32_t> plan_key(const uint32_t* q, const uint32_t* omega, uint64_t n, uint32_t limbs, int dev) {
@@ -395,24 +388,26 @@ int get_plan(const uint32_t* q, const uint32_t* omega, uint64_t n, uint32_t limb
   // fused pointwise product of a cyclic product, which leaves a factor R^-1
   const int bD = digit_bits(fe->f.L) * digit_count(fe->f.L, fe->f.fw);
   const int D = digit_count(fe->f.L, fe->f.fw);
-  std::vector<uint32_t> sc((size_t)4 * D);
+  // one buffer and one copy for the scales and both ladders (a plan's host time
+  // is mostly its device allocations and copies)
+  const size_t lw = ladder_words(*p);
+  std::vector<uint32_t> consts((size_t)4 * D + 2 * lw);
   auto scale_digits = [&](const HBig& v, uint32_t* out) {
     HBig vq;
     HBig::divmod(HBig::shl(v, bD), Q, &vq, nullptr);
     digits_of(vq, fe->f.L, fe->f.fw, out);
     digits_of(v, fe->f.L, fe->f.fw, out + D);
   };
-  scale_digits(ninv, sc.data());
-  scale_digits(HBig::mulmod(ninv, fe->adj, Q), sc.data() + 2 * D);
-  int e = upload(&p->scales, sc);
-  if (e) return hip_fail(e, "scale upload");
-  rc = build_tables(*p, W, &p->fwd);
+  scale_digits(ninv, consts.data());
+  scale_digits(HBig::mulmod(ninv, fe->adj, Q), consts.data() + 2 * D);
+  fill_ladder(*p, W, consts.data() + 4 * D);
+  fill_ladder(*p, Winv, consts.data() + 4 * D + lw);
+  int e = upload(&p->consts, consts);
+  if (e) return hip_fail(e, "plan constants upload");
+  // (on failure the plan's destructor frees what it holds)
+  rc = build_table(*p, p->consts + 4 * D, &p->fwd);
+  if (!rc) rc = build_table(*p, p->consts + 4 * D + lw, &p->inv);
   if (rc) return rc;
-  rc = build_tables(*p, Winv, &p->inv);
-  if (rc) {
-    free_tables(&p->fwd);  // (the plan's destructor would too; freed here so the failure path holds nothing)
-    return rc;
-  }
   e = (int)hipDeviceSynchronize();
   if (e) return hip_fail(e, "plan build");
   std::lock_guard<std::mutex> lk(g_mu);

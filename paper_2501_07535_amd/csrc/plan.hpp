@@ -26,8 +26,7 @@ struct FieldEntry {
 };
 
 struct DirTables {
-  uint32_t* tw = nullptr;      // n entries x tw_words(L) words: quotient and twiddle digits
-  uint32_t* ladder = nullptr;  // (logn + 2) x L words: w^(2^b) in Montgomery form, then 1, then 2^(bD) mod q
+  uint32_t* tw = nullptr;  // n entries x tw_words(L) words: quotient and twiddle digits
 };
 
 struct NttPlan {
@@ -36,9 +35,11 @@ struct NttPlan {
   uint64_t n = 0;
   uint32_t logn = 0;
   DirTables fwd, inv;
-  uint32_t* scales = nullptr;     // the inverse's last-pass factor (2 D digits), then the one after a pointwise product
-  const uint32_t* inv_scale() const { return scales; }
-  const uint32_t* mul_scale() const { return scales + 2 * digit_count(fe->f.L, fe->f.fw); }
+  // the inverse's last-pass factor (2 D digits), the one after a pointwise
+  // product, then each direction's ladder
+  uint32_t* consts = nullptr;
+  const uint32_t* inv_scale() const { return consts; }
+  const uint32_t* mul_scale() const { return consts + 2 * digit_count(fe->f.L, fe->f.fw); }
   uint32_t* scratch = nullptr;    // for in-place multi-pass calls
   uint32_t* spectra = nullptr;    // 2 x n x L words: the two forward transforms of a cyclic product
   NttSchedule sched;
@@ -46,10 +47,8 @@ struct NttPlan {
   std::mutex mu;  // guards scratch allocation and schedule changes
   ~NttPlan() {
     (void)hipFree(fwd.tw);
-    (void)hipFree(fwd.ladder);
     (void)hipFree(inv.tw);
-    (void)hipFree(inv.ladder);
-    (void)hipFree(scales);
+    (void)hipFree(consts);
     (void)hipFree(scratch);
     (void)hipFree(spectra);
   }

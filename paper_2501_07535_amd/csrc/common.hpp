@@ -35,9 +35,17 @@ constexpr int barrett_off(int L, bool fw = false) {
 // bits 96.4 and 94.0, 128 bits 127.0 and 127.2; full-width vmul at 64 bits 71.0
 // and 67.0, 96 bits 97.4 and 95.9, 128 bits 126.3 and 127.0.
 constexpr int kWordLimbsVmul = 4, kWordLimbs = 3;
-// words of one twiddle table entry: the quotient's digits, the twiddle's
-// digits, padded to whole 16-byte loads
-constexpr int tw_words(int L, bool fw = false) { return (2 * digit_count(L, fw) + 3) / 4 * 4; }
+// Words of one twiddle table entry: the quotient's digits and the twiddle's, and
+// above 4 limbs up to whole 16-byte loads.  At 2 and 4 limbs that would make
+// entries of 8 words for 6 and of 12 for 10, and long transforms read the whole
+// table: padded and not, 2^24 points 447 and 425 us at 64 bits, 916 and 887 at 128
+// (2^20: 37.0 and 38.5, 61.6 and 61.1).  Wider entries waste less, and a last load
+// of 8 bytes costs what it saves or more: 2^20 points at 256 bits 112 and 115 us,
+// 2^14 at 640 bits 54.4 and 56.7.
+constexpr int tw_words(int L, bool fw = false) {
+  const int d2 = 2 * digit_count(L, fw);
+  return L <= 4 ? d2 : (d2 + 3) / 4 * 4;
+}
 
 // widest limb counts that get radix-4 / radix-8 / radix-16 register units
 // (radix 4 up to 16 limbs: 4 elements of 16 limbs plus the digit multiply fit
@@ -99,7 +107,7 @@ struct NttPassArgs {
   uint32_t* out;
   const uint32_t* scale;  // last pass of the inverse: the factor every element takes on store, else NULL (2 D digits:
                           // its quotient's, then its own, as a twiddle's)
-  const uint32_t* tw;  // twiddle table, element-major, tw_words(L) words per entry
+  const uint32_t* tw;  // twiddle table: tw_words(L) words per entry, in planes of 16 bytes (ntt_impl.hpp, Twiddle)
   uint64_t n;
   uint32_t logn, K, k, logc;
   uint32_t last;       // last pass: store canonical residues in [0, q)

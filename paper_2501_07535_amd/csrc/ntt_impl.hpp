@@ -73,8 +73,9 @@ struct NttC : OffsetC<L, !FW && (offset_applies(L, 1) || offset_applies(L, 2))> 
 __device__ __forceinline__ u32 rev_bits(u32 x, u32 b) { return b ? (__brev(x) >> (32 - b)) : 0u; }
 
 // One twiddle: its quotient's digits, then its own, tw_words(L, FW) words.  The
-// table holds them in 16-byte pieces, piece c of entry e at word 4 (c n + e):
-// the lanes of a load read consecutive pieces, whatever the entry's length.
+// table holds them in 16-byte pieces, piece c of entry e at word 4 (c n + e), and
+// where two words are left over, in a last plane of 8-byte ones: the lanes of a
+// load read consecutive pieces, whatever the entry's length.
 // `first` (the level's first entry plus the unit's, uniform) and the lane's
 // offset `off` < 2^25 entries keep the lane's part of the address in 32 bits.
 template <int L, bool FW = false>
@@ -87,13 +88,19 @@ struct Twiddle {
     // (opaque here, or the bases of a whole round are computed ahead of it and
     // spilled)
     asm volatile("" : "+s"(first));
+    constexpr int S = tw_words(L, FW);
 #pragma unroll
-    for (int i = 0; i < tw_words(L, FW) / 4; i++) {
+    for (int i = 0; i < S / 4; i++) {
       const uint4 t = uniform_at<uint4>(tw + 4 * (i * n + first), off << 4);
       v[4 * i] = t.x;
       v[4 * i + 1] = t.y;
       v[4 * i + 2] = t.z;
       v[4 * i + 3] = t.w;
+    }
+    if constexpr (S % 4) {
+      const uint2 t = uniform_at<uint2>(tw + (S - 2) * n + 2 * first, off << 3);
+      v[S - 2] = t.x;
+      v[S - 1] = t.y;
     }
   }
 };
@@ -873,6 +880,7 @@ __global__ __launch_bounds__(256) void twiddle_kernel(u32* __restrict__ tw, u64 
   uint4* out = reinterpret_cast<uint4*>(tw);
 #pragma unroll
   for (int j = 0; j < S / 4; j++) out[j * n + e] = make_uint4(d[4 * j], d[4 * j + 1], d[4 * j + 2], d[4 * j + 3]);
+  if constexpr (S % 4) reinterpret_cast<uint2*>(tw + (S - 2) * n)[e] = make_uint2(d[S - 2], d[S - 1]);
 }
 
 template <int L, bool FW = false>

@@ -1,7 +1,8 @@
 """CPU-only count of what the library asks of the device when a plan and a batch
 are created: their host time is mostly device allocations and copies, so a plan
 makes three allocations (constants, two twiddle tables) and one copy, and a
-batch one of each for all of its tables, whatever its number of launches.
+batch one of each for all of its tables, whatever its number of launches; and of
+the bytes a plan holds, which at 2 and 4 limbs have no padding.
 
 The HIP runtime's calls are counted by a small stand-in, preloaded into a child
 process, that gives out host memory and launches nothing."""
@@ -17,8 +18,8 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 STUB = r"""
 #include <stdlib.h>
 #include <string.h>
-int stub_allocs, stub_copies, stub_frees;
-int hipMalloc(void** p, size_t n) { stub_allocs++; *p = malloc(n); return *p == 0 ? 2 : 0; }
+int stub_allocs, stub_copies, stub_frees, stub_bytes;
+int hipMalloc(void** p, size_t n) { stub_allocs++; stub_bytes += n; *p = malloc(n); return *p == 0 ? 2 : 0; }
 int hipFree(void* p) { if (p) stub_frees++; free(p); return 0; }
 int hipMemcpy(void* d, const void* s, size_t n, int k) { (void)k; stub_copies++; memcpy(d, s, n); return 0; }
 int hipGetDevice(int* d) { *d = 0; return 0; }
@@ -53,13 +54,13 @@ sys.path.insert(0, sys.argv[1])
 import moma_inputs as mi
 import paper_2501_07535_amd as moma
 lib, stub = moma.library(), ctypes.CDLL(sys.argv[2])
-counts = [ctypes.c_int.in_dll(stub, n) for n in ("stub_allocs", "stub_copies", "stub_frees")]
+counts = [ctypes.c_int.in_dll(stub, n) for n in ("stub_allocs", "stub_copies", "stub_frees", "stub_bytes")]
 def counted(f):
     for c in counts: c.value = 0
     assert f() == 0
     return [c.value for c in counts]
 def words(v, L): return (ctypes.c_uint32 * L)(*[(v >> (32 * j)) & 0xFFFFFFFF for j in range(L)])
-fields = [mi.find_prime(lam, 0) for lam in (64, 256, 384)]
+fields = [mi.find_prime(lam, 0) for lam in (64, 128, 256, 384)]
 roots = [f.root(1 << 12) for f in fields]
 for f, w in zip(fields, roots):
     print("plan", *counted(lambda: lib.moma_ntt_prepare(words(f.q, f.limbs), words(w, f.limbs), 1 << 12, f.limbs)))
@@ -97,6 +98,11 @@ def test_plans_and_batches_are_created_with_few_allocations(tmp_path):
     got = {}
     for name, *v in rows:
         got.setdefault(name, []).append([int(x) for x in v])
-    assert len(got["plan"]) == 3 and all(v[:2] == [3, 1] for v in got["plan"]), got
-    assert got["batch"] == [[1, 1, 0]], got
-    assert got["destroy"] == [[0, 0, 1]] and got["shutdown"] == [[0, 0, 9]], got
+    assert len(got["plan"]) == 4 and all(v[:2] == [3, 1] for v in got["plan"]), got
+    assert [v[:3] for v in got["batch"]] == [[1, 1, 0]], got
+    assert got["destroy"] == [[0, 0, 1, 0]] and got["shutdown"] == [[0, 0, 12, 0]], got
+    # two tables of 2^12 entries: twice the digits (3, 5, 9 and 14 of 29 bits), padded
+    # to whole 16 bytes above 4 limbs only; the rest is the constants
+    for L, digits, padded, v in zip((2, 4, 8, 12), (3, 5, 9, 14), (6, 10, 20, 28), got["plan"]):
+        consts = 4 * (4 * digits + 2 * 14 * L)
+        assert v[3] == 2 * 4 * padded * (1 << 12) + consts, (L, v)

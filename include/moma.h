@@ -118,7 +118,7 @@ int moma_unpack_planar(uint32_t limbs, uint64_t n, const uint32_t* d_planar, uin
  *   moma_vadd: out_i = (a_i + b_i) mod q
  *   moma_vsub: out_i = (a_i - b_i) mod q
  *   moma_vmul: out_i = (a_i * b_i) mod q      (Barrett reduction, Eq. (barrett))
- *   moma_axpy: out_i = (alpha * x_i + y_i) mod q   (alpha kept with its quotient)
+ *   moma_axpy: out_i = (alpha * x_i + y_i) mod q   (alpha prepared once)
  * n is the element count (0 is a no-op).  Device arrays are limb-planar with
  * `limbs` planes of n words.  alpha is a host scalar in [0, q).
  */

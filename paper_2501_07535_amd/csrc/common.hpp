@@ -69,9 +69,11 @@ struct FieldRaw {
   uint32_t q[kMaxLimbs];
   uint32_t qinv;           // -q^{-1} mod 2^32 (Montgomery)
   uint32_t one_m[kMaxLimbs];  // 2^(32L) mod q (1 in Montgomery form)
-  uint32_t qn[kMaxLimbs];  // q * 2^d, bitlen 32L - 4 (Barrett)
+  // vmul on words (up to kWordLimbsVmul limbs, and its Karatsuba variant); d and
+  // qn's top limb, in cinv, are also the lazy butterflies' quotient estimate
+  uint32_t qn[kMaxLimbs];  // q * 2^d, bitlen 32L - 4
   uint32_t mu[kMaxLimbs];  // floor(2^(2(32L-4)+3) / qn)
-  uint32_t d;              // Barrett pre-scale shift
+  uint32_t d;              // bits that q lacks to 32L - 4
   uint32_t vd;             // vmul in digits: bits that q lacks to W0 (barrett_off)
   uint32_t vmu[40];        // and its quotient constant, the top digit with the bits above bD
   uint32_t vnqn[40];       // 2^(bD) minus the scaled modulus, in digits
@@ -89,8 +91,8 @@ struct BlasArgs {
   uint32_t* out;
   uint64_t n;
   uint32_t alpha_m[kMaxLimbs];  // axpy: alpha 2^(32L) mod q (the word form)
-  uint32_t alpha_d[40];  // alpha in digits
-  uint32_t alpha_q[40];  // and its quotient floor(alpha 2^(bD) / q)
+  uint32_t alpha_d[40];         // alpha in digits
+  uint32_t alpha_q[40];         // and its quotient floor(alpha 2^(bD) / q)
   uint32_t variant;      // vmul: 0 schoolbook products, 1 Karatsuba (L >= 2)
   uint32_t ls;           // storage planes (>= L; the planes above L are written as zero)
 };

@@ -625,28 +625,27 @@ __device__ __forceinline__ void ct_butterfly_one(u32* x, u32* y, const u32* q2v)
 // Lazy butterflies.  With 4 spare bits above q (and digits that cover all 32L
 // bits: spare_bits, every headroom limb count but 10) a value may be anything
 // in [0, 16q), and a multiplying butterfly is two additions,
-//   t <- w*y in [0, g q);  x' = x + t;  y' = x - t,   g = 1 + 2^(32L-bD) + 2^-24,
-// as long as x stays between t and 16q - t: stages move the bounds by g q each
-// way (growth_64th, in 64ths).  Where the next stages would leave [0, 16q), the
-// x of the first of them are moved to [7q, 8q] (offset_reduce): with five or six
-// stages in a pass that is once per pass, against a trial subtraction of x and
-// an addition of 2q in every butterfly (Harvey, "Faster arithmetic for
-// number-theoretic transforms", J. Symb. Comp. 2014: values in [0, 4q)).
+//   t <- w*y in [0, g q);  x' = x + t;  y' = x - t,   g = 1 + 2^(32L-bD) + e,
+// where e < (D - 2) 2^-b is what the quotient's dropped columns weigh (2^-22.9 at
+// 32 limbs), as long as x stays between t and 16q - t: stages move the bounds by
+// g q each way (growth_64th, in 64ths, with 1/64 for e).  Where the next stages
+// would leave [0, 16q), the x of the first of them are moved to 7q and up to 1/64
+// above 8q (offset_reduce): with five or six stages in a pass that is once per
+// pass, against a trial subtraction of x and an addition of 2q in every butterfly
+// (Harvey, "Faster arithmetic for number-theoretic transforms", J. Symb. Comp.
+// 2014: values in [0, 4q)).
 constexpr int spare_bits(int L) { return digit_bits(L) * digit_count(L) - 32 * L; }
 constexpr u32 growth_of(int spare) { return 64 + (64 >> (spare < 0 ? 0 : spare < 6 ? spare : 6)) + 1; }
 template <int L>
 constexpr u32 growth_64th = growth_of(spare_bits(L));
 
 // r = x - (f - off) q for x in [0, 16q), where f is floor(x / q) or, when x / q
-// is within 2^-24 above it, one less: r in [off q, (off + 1 + 2^-24) q).  f comes
-// from the top 32 bits of x 2^d; the multiple of q is formed in signed words.
+// is less than 19 2^-27 above it, one less: r in [off q, (off + 1 + 19 2^-27) q)
+// (the bounds of a pass take 1/64 for it).  f comes from the top 32 bits of x 2^d
+// and cinv; the multiple of q is formed in signed words.
 template <int L>
 __device__ __forceinline__ void offset_reduce(u32* x, u32 off, const u32* qsw, u32 d, u32 cinv) {
-  u32 xt;
-  if constexpr (L == 1)
-    xt = x[0] << d;
-  else
-    xt = (u32)((((u64)x[L - 1] << 32 | x[L - 2]) << d) >> 32);
+  const u32 xt = (u32)((((u64)x[L - 1] << 32 | x[L - 2]) << d) >> 32);
   const int k = (int)(off - (__umulhi(xt, cinv) >> 26));
   u32 p[L];
   int64_t acc = 0;

@@ -53,7 +53,8 @@ def issue_costs(rates: dict) -> tuple[float, float]:
 
 
 def multiply_forms(L: int, rates: dict) -> dict:
-    """Work of one L-limb Montgomery multiply in peak lane-ops, in its two
+    """The unit of comparison between multiplies, not what the kernels issue
+    (issued_butterfly_ops): work of one L-limb Montgomery multiply in peak lane-ops, in its two
     gfx950 forms.  Word form: P(L) 32-bit word products, each a v_mad_u64_u32
     plus the v_addc_co_u32 that takes its carry.  Digit form (the same
     multiply on D digits of b bits, b = 29 up to 28 limbs, else 28, D =
@@ -70,7 +71,7 @@ def multiply_forms(L: int, rates: dict) -> dict:
 
 
 def butterfly_slots(L: int, rates: dict) -> float:
-    """Work of one butterfly under the op model, in peak lane-ops: one L-limb
+    """Work of one butterfly in that unit, in peak lane-ops: one L-limb
     Montgomery multiply in the cheaper of its two forms (multiply_forms) plus
     a modular add and a modular subtract (3L add-class ops each: the chain,
     the trial subtraction, the select)."""
@@ -79,20 +80,66 @@ def butterfly_slots(L: int, rates: dict) -> float:
     return min(f["word"], f["digit"]) + 6 * L * ca
 
 
-def blas_slots(op: str, L: int, rates: dict, karatsuba: bool = False) -> float:
-    """Work per element of one BLAS op under the same op model, in peak lane-ops.  vmul
-    (Barrett): two full L x L products (3 ceil(L/2)^2 word products each by
-    Karatsuba, else L^2) and the low half of r2 * q (L(L+1)/2), plus 3L for the
-    subtraction and correction; axpy: a Montgomery multiply by alpha (P(L))
-    with its correction (2L) and a modular add (3L); vadd/vsub: 3L."""
+def digits_of(L: int, full: bool = False) -> tuple[int, int]:
+    """(b, D): bits and count of the digits the kernels multiply in."""
+    b = 29 if L <= 28 else 28
+    return b, -(-(32 * L - (0 if full else 1)) // b)
+
+
+def product_counts(L: int, full: bool = False) -> dict:
+    """Digit products (one v_mad_u64_u32 each) of one twiddle multiply as the
+    transform kernels issue it: the quotient's columns D-2 .. 2D-2, then the low
+    D columns of w y and of m (R - q); karatsuba: w y's low columns from the low
+    halves' product whole and the two others up to column D - h."""
+    b, D = digits_of(L, full)
+    h = (D + 1) // 2
+    g, cut = D - h, D - h
+    quot, low = D * (D + 1) // 2 + D - 1, D * (D + 1) // 2
+    z0 = h * h
+    zm = cut * (cut + 1) // 2
+    z2 = sum(1 for c in range(cut) for i in range(c + 1) if i < g and c - i < g)
+    return {"schoolbook": quot + 2 * low, "karatsuba": quot + z0 + zm + z2 + low}
+
+
+def issued_butterfly_ops(L: int, radix_log: int, karatsuba: bool, rates: dict, full: bool = False) -> dict:
+    """What one multiplying butterfly issues, and its time at the measured rates
+    in peak lane-ops: the digit products, two add-class ops per column (shift and
+    mask), and the additions: 2L where values run over [0, 16q) (radix 4 from 6
+    limbs, radix 2 from 20, except where the digits fall short of 32L bits, the
+    Karatsuba form and full width), else 5L (8L full width).  Addresses, loads,
+    stores and the digits' packing are not in it."""
+    b, D = digits_of(L, full)
+    products = product_counts(L, full)["karatsuba" if karatsuba else "schoolbook"]
+    offset = not full and not karatsuba and b * D >= 32 * L and (
+        (radix_log == 2 and L >= 6) or (radix_log == 1 and L >= 20))
+    adds = (2 if offset else 8 if full else 5) * L
     cm, ca = issue_costs(rates)
+    return {"digits": D, "products": products, "add_class_ops": adds,
+            "lane_ops": products * PEAK_INT_OPS / rates["mad_u64_u32"] + (2 * (2 * D + 1) + adds) * ca}
+
+
+def blas_slots(op: str, L: int, rates: dict, karatsuba: bool = False) -> float:
+    """Work per element of one BLAS op as issued, at the measured rates in peak
+    lane-ops.  vmul (Barrett) up to 4 limbs and by Karatsuba: on words, two full L x L
+    products (3 ceil(L/2)^2 word products each by Karatsuba, else L^2) and the low
+    half of r2 * q (L(L+1)/2), else 2D^2 + 2D digit products with two add-class ops
+    per column, plus 3L for the subtraction and correction; axpy: up to 3 limbs a
+    Montgomery multiply by alpha on words (P(L)), else the transform's product, with
+    its correction (2L) and a modular add (3L); vadd/vsub: 3L."""
+    cm, ca = issue_costs(rates)
+    b, D = digits_of(L)
+    mad = PEAK_INT_OPS / rates["mad_u64_u32"]
     if op in ("vadd", "vsub"):
         return 3 * L * ca
     if op == "vmul":
-        h, g = (L + 1) // 2, L // 2
-        full = 2 * h * h + g * g if karatsuba else L * L
-        return (2 * full + L * (L + 1) // 2) * cm + 3 * L * ca
-    return word_products(L) * cm + 5 * L * ca
+        if karatsuba or L <= 4:
+            h, g = (L + 1) // 2, L // 2
+            whole = 2 * h * h + g * g if karatsuba else L * L
+            return (2 * whole + L * (L + 1) // 2) * cm + 3 * L * ca
+        return (2 * D * D + 2 * D) * mad + (2 * (4 * D) + 3 * L) * ca
+    if L <= 3:
+        return word_products(L) * cm + 5 * L * ca
+    return product_counts(L)["schoolbook"] * mad + (2 * (2 * D + 1) + 5 * L) * ca
 
 
 def host_cpu() -> dict:
@@ -190,11 +237,13 @@ def sweep(args):
         st = steady_state(moma, torch, stream, dx, q, w, n, L, logn,
                           ks=tuple(sorted({k for k in (1, 4, 16, 64) if k <= kmax} | {kmax})), settle=args.settle)
         B = n // 2 * logn
+        sch = moma.ntt_get_schedule(q, w, n, L)
         print(json.dumps({"lambda": lam, "limbs": L, "q_bits": q.bit_length(), "full_width": bool(bits),
                           "log2_n": logn, "fwd_us": round(us, 2),
                           "gbutterfly_s": round(B / us / 1e3, 3), "steady_state": st,
-                          "schedule": list(moma.ntt_get_schedule(q, w, n, L)),
-                          "alu_frac": round(butterfly_slots(L, rates) * B / (us * 1e-6) / PEAK_INT_OPS, 4),
+                          "schedule": list(sch),
+                          "alu_frac": round(issued_butterfly_ops(L, sch[3], bool(sch[4]), rates, bool(bits))["lane_ops"]
+                                            * B / (us * 1e-6) / PEAK_INT_OPS, 4),
                           "sampled_vs_oracle": ok}), flush=True)
         del dx, dy
         moma.shutdown()
@@ -302,11 +351,9 @@ def mulalg(args):
             us = _time_fwd(moma, torch, stream, dx, dy, q, w, 5, 200)
             ok &= bool((mi.from_planar(dy.cpu().numpy().view(np.uint32)) == want).all())
             res[name] = {"schedule": list(sch), "us": round(us, 3)}
-        D = -(-(32 * L - 2) // (29 if L <= 28 else 28))
-        h, g = (D + 1) // 2, D // 2
+        D = digits_of(L)[1]
         print(json.dumps({"lambda": lam, "limbs": L, "digits": D, "log2_n": logn,
-                          "digit_products_per_multiply": {"schoolbook": 2 * D * D,
-                                                          "karatsuba": 2 * h * h + g * g + D * D},
+                          "digit_products_per_multiply": product_counts(L),
                           **res,
                           "karatsuba_over_schoolbook_best": round(res["karatsuba_best"]["us"] /
                                                                   res["schoolbook_best"]["us"], 3),
@@ -332,9 +379,11 @@ def peaks():
            "hbm_TBs": {"copy": round(r["hbm_copy"] / 1e12, 3), "triad": round(r["hbm_triad"] / 1e12, 3)},
            "of_hbm_peak": {"copy": round(r["hbm_copy"] / PEAK_HBM, 4), "triad": round(r["hbm_triad"] / PEAK_HBM, 4)},
            "lane_ops_per_word_product_with_carry": round(cm, 4), "lane_ops_per_add_op": round(ca, 4),
-           "lane_ops_multiply": {str(L): {k: round(v, 1) for k, v in multiply_forms(L, r).items()}
+           "unit_lane_ops_multiply": {str(L): {k: round(v, 1) for k, v in multiply_forms(L, r).items()}
                                  for L in (2, 4, 8, 12, 16, 24, 32)},
-           "lane_ops_per_butterfly": {str(L): round(butterfly_slots(L, r), 1) for L in (2, 4, 8, 12, 16, 24, 32)},
+           "unit_lane_ops_per_butterfly": {str(L): round(butterfly_slots(L, r), 1) for L in (2, 4, 8, 12, 16, 24, 32)},
+           "issued_per_butterfly": {str(L): {k: round(v, 1) for k, v in issued_butterfly_ops(
+               L, 2 if L <= 10 else 1, False, r).items()} for L in (2, 4, 8, 12, 16, 24, 32)},
            "compute_units": r["compute_units"]}
     print(json.dumps(out), flush=True)
 
@@ -442,7 +491,9 @@ def main():
     launch_ms = ms_step / launches
     # issue rates measured on this device after the timed region
     rates = moma.measure_peaks()
-    slots = butterfly_slots(L, rates)
+    sched = moma.ntt_get_schedule(q, w, n, L)
+    ops = issued_butterfly_ops(L, sched[3], bool(sched[4]), rates, q.bit_length() > 32 * L - 4)
+    slots = ops["lane_ops"]
     achieved = slots * B / launches / (launch_ms * 1e-3) / 1e12
     peak = PEAK_INT_OPS / 1e12
     counters = committed_counters(lam, logn, moma.ntt_get_schedule(q, w, n, L), plan["stages"])
@@ -451,7 +502,6 @@ def main():
         # wave instructions x 4 cycles each over the SIMD-cycles of one launch
         valu_issue = counters["sq_insts_valu_per_launch"] * 4 / (VALU_SIMDS * CLOCK_HZ * launch_ms * 1e-3)
     cm, ca = issue_costs(rates)
-    mf = multiply_forms(L, rates)
 
     if args.calib_copy_mib:
         src = torch.zeros(args.calib_copy_mib << 18, dtype=torch.int32, device=dev)
@@ -499,13 +549,13 @@ def main():
                      "launches_per_step": launches,
                      "avg_launch_us": round(launch_ms * 1e3, 3),
                      "avg_launch_us_from": "HIP events over the timed region / launches",
-                     "op_model": {"word_products_per_multiply": word_products(L),
-                                  "digit_products_per_multiply": 2 * mf["digits"] ** 2,
-                                  "lane_ops_multiply_word_form": round(mf["word"], 2),
-                                  "lane_ops_multiply_digit_form": round(mf["digit"], 2),
-                                  "add_class_ops_per_butterfly": 6 * L,
+                     "op_model": {"digits": ops["digits"],
+                                  "digit_products_per_multiply": ops["products"],
+                                  "add_class_ops_per_butterfly": ops["add_class_ops"],
                                   "lane_ops_per_add_op": round(ca, 4),
                                   "lane_ops_per_butterfly": round(slots, 2)},
+                     "montgomery_unit": {"lane_ops_per_butterfly": round(butterfly_slots(L, rates), 2),
+                                         "Tops_s": round(butterfly_slots(L, rates) * B / (ms_step * 1e-3) / 1e12, 3)},
                      "measured_rates_Tops": {k: round(rates[k] / 1e12, 3) for k in
                                              ("add_u32", "add_co_addc_u32", "mad_u64_u32", "mad_addc_u32",
                                               "mul_lo_u32", "mul_hi_u32")},

@@ -166,18 +166,24 @@ static int batch_create(const moma_ntt_job_t* jobs, uint32_t njobs, BatchImpl& b
     std::vector<uint2> items;
   };
   std::map<std::tuple<int, int, uint32_t, bool>, BGroup> bgroups;
-  // Waves of radix-2 units of one pass, per compute limb count (each limb count
-  // is a chain of launches of its own): below four for every SIMD of the chip the
-  // chain is sparse, and its small jobs take shapes for the shortest way through
-  // their passes (batch_schedule, where both sides are measured).
-  constexpr uint64_t kSparseWaves = 4 * 1024;
+  // What the jobs of each compute limb count bring: a small job's shape goes by it
+  // (batch_schedule).  Transforms of less than a wave count for nothing: they are
+  // over after one short pass, and the larger jobs beside them run as if alone.
+  // (256 bits, 4 jobs of 2^12 points among 10000 of 64: 69 us so, 104 with the shapes
+  // for a full chip; 64 bits, 2 of 2^16 among 20000: 44 and 85.)
   constexpr uint64_t kSmallJob = 1ull << 18;
-  std::map<int, uint64_t> waves;
+  std::map<int, ChainLoad> loads;
   for (uint32_t j = 0; j < njobs; j++) {
     std::shared_ptr<FieldEntry> fe;
     std::string keep = g_detail;
-    if (jobs[j].kind < MOMA_JOB_VADD && build_field(jobs[j].q, jobs[j].limbs, &fe) == MOMA_OK)
-      waves[fe->f.L] += jobs[j].n / 128 * (jobs[j].kind == MOMA_JOB_CYCLIC_MUL ? 2 : 1);
+    if (jobs[j].kind < MOMA_JOB_VADD && jobs[j].n >= 128 && build_field(jobs[j].q, jobs[j].limbs, &fe) == MOMA_OK) {
+      const uint64_t transforms = jobs[j].kind == MOMA_JOB_CYCLIC_MUL ? 2 : 1;
+      ChainLoad& load = loads[fe->f.L];
+      load.waves += jobs[j].n / 128 * transforms;
+      load.jobs += transforms;
+      load.least = std::min(load.least, jobs[j].n);
+      load.most = std::max(load.most, jobs[j].n);
+    }
     g_detail = keep;  // (a job that fails is reported in its turn below)
   }
   // groups of large jobs: the phases [group_phase, group_phase + group_span)
@@ -247,7 +253,7 @@ static int batch_create(const moma_ntt_job_t* jobs, uint32_t njobs, BatchImpl& b
     // and workgroups); larger jobs keep their schedule, which measured faster
     // for them (2^24 points, and 1024-bit moduli at 2^20).
     if (p->n <= kSmallJob) {
-      NttSchedule ds = batch_schedule(f.L, p->logn, waves[f.L] <= kSparseWaves);
+      NttSchedule ds = batch_schedule(f.L, p->logn, loads[f.L]);
       std::vector<NttPass> dp;
       std::string keep = g_detail;
       if (plan_passes(f.L, p->logn, ds, &dp, f.fw) == MOMA_OK) {

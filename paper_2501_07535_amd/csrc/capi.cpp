@@ -227,31 +227,51 @@ NttSchedule default_schedule(int L, uint32_t logn) {
   return first_feasible(L, logn, shapes, std::min(L <= 10 ? 2u : 1u, max_radix_log(L)), 256);
 }
 
-// Shape for a small job inside a batch.
-// Where the batch's other jobs of this limb count fill the chip: one pass when
-// the transform fits a 64 KiB tile, else the largest tiles (fewest passes) with
-// 32 or 16 columns, in radix-4 units up to 8 limbs (64 transforms of 2^16
-// points: 352 bits 539 us with radix-2 units against 638, 384 bits 564 against 677;
-// 288 bits 382 against 394; but 256 bits 323 against 297).
-// `sparse`, where they do not (batch.cpp draws the line): 32 KiB tiles, radix-2
-// units and up to 512 threads, for the shortest way through each job's passes
-// (2 mixed jobs 80 -> 62 us, 16: 173 -> 132, 40: 233 -> 149, 100: 288 -> 207; 4
-// transforms of 2^16 points at 256 bits 56 -> 45 us; but 16 of them 96 -> 118).
-NttSchedule batch_schedule(int L, uint32_t logn, bool sparse) {
+// Shape for a small job inside a batch, by what the batch's jobs of this limb count
+// (a chain of launches of its own) bring: the waves of radix-2 units in one pass of
+// them all, and their number.
+// Where they fill the chip: one pass when the transform fits a 64 KiB tile, else
+// the largest tiles (fewest passes) with 32 or 16 columns, in radix-4 units up to
+// 8 limbs (64 transforms of 2^16 points: 352 bits 539 us with radix-2 units against
+// 638, 384 bits 564 against 677; 288 bits 382 against 394; but 256 bits 323 against
+// 297).
+// Where they are sparse: 32 KiB tiles, radix-2 units and up to 512 threads, for the
+// shortest way through each job's passes (2 mixed jobs 80 -> 62 us, 16: 173 -> 132,
+// 40: 233 -> 149, 100: 288 -> 207).  The line, in waves on every SIMD:
+//   up to 8 limbs 4; from 5 limbs 2 if the transforms have no more than 2^13 points
+//     on average (256 of 2^11 points: sparse 59 us at 256 bits, 54 at 224, full 46
+//     and 41; 100 mixed jobs of 2^10 to 2^16: 284 and 332);
+//   from 9 limbs 1 (256 of 2^10: 51 and 42 at 384 bits; 8 of 2^16: 128 and 88 at 320,
+//     180 and 148 at 512; mixed jobs, too), but 3 if all have one size above 2^13 and
+//     the smaller tile needs no more passes (12 of 2^15 at 352 bits 80 and 96);
+//   above 16, where the shapes differ in the tile alone, 4, and full where the
+//     smaller tile needs a pass more (1024 bits: 256 of 2^10 in 3 and 2 passes 244 and
+//     165, 16 of 2^14 290 and 249; 64 of 2^12 in as many 198 and 296).
+NttSchedule batch_schedule(int L, uint32_t logn, const ChainLoad& load) {
+  const uint64_t simds = 4ull * device_cu_count();
+  const bool small = load.waves <= 64 * load.jobs;  // 2^13 points are 64 waves
   uint32_t t64 = tile_log_for(16384u / (uint32_t)L), t32 = tile_log_for(8192u / (uint32_t)L);
-  if (sparse) {
-    std::vector<std::pair<uint32_t, uint32_t>> shapes;
-    if (logn <= t32) shapes.push_back({logn, 0});
-    for (uint32_t cl : {5u, 4u, 3u, 2u, 1u}) shapes.push_back({t32, cl});
-    for (uint32_t cl : {2u, 1u}) shapes.push_back({t64, cl});
-    return first_feasible(L, logn, shapes, 1, 512);
-  }
   std::vector<std::pair<uint32_t, uint32_t>> shapes;
   if (logn <= t64) shapes.push_back({logn, 0});
   for (uint32_t cl : {5u, 4u}) shapes.push_back({t64, cl});
   for (uint32_t cl : {5u, 4u, 3u, 2u}) shapes.push_back({t32, cl});
   for (uint32_t cl : {3u, 2u, 1u}) shapes.push_back({t64, cl});
-  return first_feasible(L, logn, shapes, std::min(L <= 8 ? 2u : 1u, max_radix_log(L)), 256);
+  const NttSchedule full = first_feasible(L, logn, shapes, std::min(L <= 8 ? 2u : 1u, max_radix_log(L)), 256);
+  const bool alike = !small && load.least == load.most;
+  const uint64_t line = L <= 4 || L > 16 ? 4 : (L > 8 ? (alike ? 3 : 1) : (small ? 2 : 4));
+  if (load.waves > line * simds) return full;
+  shapes.clear();
+  if (logn <= t32) shapes.push_back({logn, 0});
+  for (uint32_t cl : {5u, 4u, 3u, 2u, 1u}) shapes.push_back({t32, cl});
+  for (uint32_t cl : {2u, 1u}) shapes.push_back({t64, cl});
+  const NttSchedule sparse = first_feasible(L, logn, shapes, 1, 512);
+  if (L <= 8 || (L <= 16 && load.waves <= simds)) return sparse;
+  std::string keep = g_detail;
+  std::vector<NttPass> few, more;
+  const bool longer = plan_passes(L, logn, full, &few) == MOMA_OK && plan_passes(L, logn, sparse, &more) == MOMA_OK &&
+                      more.size() > few.size();
+  g_detail = keep;
+  return longer ? full : sparse;
 }
 
 NttSchedule initial_schedule(int L, uint32_t logn, bool fw) {

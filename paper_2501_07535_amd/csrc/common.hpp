@@ -161,6 +161,7 @@ struct DigitConsts {
 // set the thread's error detail and return code
 int set_error(int code, const std::string& detail);
 
+uint32_t device_cu_count();
 // launchers (return hipError_t as int)
 int launch_blas(int op, const FieldRaw& f, const BlasArgs& a, hipStream_t s);
 int launch_zero_planes(uint32_t* out, uint64_t n, int from_plane, int to_plane, hipStream_t s);

@@ -935,7 +935,6 @@ constexpr bool kFusedLast = L <= 8;
 // 1 to 7% faster transforms from 64 to 256 bits at 2^19 to 2^25 points; with
 // one tile per compute unit (2^18 points, 256 bits) the load phase's wider
 // loads were 4% faster.
-uint32_t device_cu_count();
 inline bool direct_load_applies(const NttPassArgs& a, uint32_t radix_log, uint64_t tiles) {
   return !a.in2 && (a.logc == 4 || a.logc == 5) && a.k > radix_log && tiles >= 2ull * device_cu_count();
 }

@@ -64,7 +64,12 @@ int get_plan(const uint32_t* q, const uint32_t* omega, uint64_t n, uint32_t limb
 uint32_t max_radix_log(int L, bool fw = false);
 int plan_passes(int L, uint32_t logn, const NttSchedule& s, std::vector<NttPass>* out, bool fw = false);
 NttSchedule default_schedule(int L, uint32_t logn);
-NttSchedule batch_schedule(int L, uint32_t logn, bool sparse);
+// the transforms of one limb count in a batch (batch_schedule)
+struct ChainLoad {
+  uint64_t waves = 0, jobs = 0;
+  uint64_t least = ~0ull, most = 0;  // points
+};
+NttSchedule batch_schedule(int L, uint32_t logn, const ChainLoad& load);
 int run_plan(NttPlan& p, bool inverse, const uint32_t* d_in, uint32_t* d_out, hipStream_t s);
 // ext: NULL, or caller-provided device scratch of cyclic_mul_scratch_words(p)
 // words used in place of the plan's spectra buffer, so the call

@@ -279,7 +279,7 @@ NttSchedule initial_schedule(int L, uint32_t logn, bool fw) {
   NttSchedule s;
   std::vector<NttPass> ps;
   bool ok = tune_db_best(current_device_name(), L, logn, &s) && plan_passes(L, logn, s, &ps, fw) == MOMA_OK;
-  if (!ok) ok = costmodel_pick(L, logn, &s) && plan_passes(L, logn, s, &ps, fw) == MOMA_OK;
+  if (!ok) ok = costmodel_pick(L, logn, fw, &s) && plan_passes(L, logn, s, &ps, fw) == MOMA_OK;
   if (!ok) s = default_schedule(L, logn);
   g_detail = keep;
   return s;

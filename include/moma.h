@@ -251,7 +251,8 @@ typedef struct moma_ntt_schedule {
 /* Set the schedule of the plan for (q, omega, n, limbs); NULL restores the
  * plan's initial choice: the timing database's fastest schedule for this
  * (compute limbs, n) if it has one, else the loaded cost model's top-ranked
- * schedule of those the modulus can run, else the fixed rule of moma_ntt_default_schedule.  New plans
+ * schedule (for a full-width modulus without the Karatsuba form) if the
+ * modulus can run it, else the fixed rule of moma_ntt_default_schedule.  New plans
  * start with that same choice.  MOMA_E_UNSUPPORTED if the shape cannot run
  * this size, MOMA_E_ARG for malformed values.  Affects calls enqueued
  * afterwards. */

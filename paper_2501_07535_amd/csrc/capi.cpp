@@ -279,7 +279,13 @@ NttSchedule initial_schedule(int L, uint32_t logn, bool fw) {
   NttSchedule s;
   std::vector<NttPass> ps;
   bool ok = tune_db_best(current_device_name(), L, logn, &s) && plan_passes(L, logn, s, &ps, fw) == MOMA_OK;
-  if (!ok) ok = costmodel_pick(L, logn, fw, &s) && plan_passes(L, logn, s, &ps, fw) == MOMA_OK;
+  // (A full-width modulus has no Karatsuba form, and takes the same shape without.
+  // Where it cannot run the shape at all, a radix-8 unit, the fixed rule is better
+  // than the model's best of the others: 2^20 points at 128 bits 63 and 70 us.)
+  if (!ok && costmodel_pick(L, logn, &s)) {
+    if (fw) s.kara = 0;
+    ok = plan_passes(L, logn, s, &ps, fw) == MOMA_OK;
+  }
   if (!ok) s = default_schedule(L, logn);
   g_detail = keep;
   return s;

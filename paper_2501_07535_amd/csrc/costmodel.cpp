@@ -21,7 +21,6 @@
 #include <map>
 #include <mutex>
 #include <string>
-#include <tuple>
 #include <vector>
 
 #include "../../include/moma.h"
@@ -51,8 +50,8 @@ struct CostModel {
 static std::mutex g_cm_mu;
 static CostModel g_cm;
 static uint64_t g_cm_gen = 0;  // bumped whenever the model changes
-// the model's pick per (compute limbs, log2 n, full width), valid for model generation g_pick_gen
-static std::map<std::tuple<int, uint32_t, bool>, NttSchedule> g_pick;
+// the model's pick per (compute limbs, log2 n), valid for model generation g_pick_gen
+static std::map<std::pair<int, uint32_t>, NttSchedule> g_pick;
 static uint64_t g_pick_gen = 0;
 
 static uint64_t sm64(uint64_t key, uint64_t i) {
@@ -113,11 +112,8 @@ int costmodel_scores(int L, uint32_t logn, const std::vector<NttSchedule>& cands
   return predict_locked(f.data(), (uint32_t)cands.size(), scores->data());
 }
 
-// The candidate with the lowest predicted time.  (A full-width modulus has fewer
-// of them, no Karatsuba form among them: the best of those, not the fixed rule
-// where the best of all is one that it cannot run.)
-bool costmodel_pick(int L, uint32_t logn, bool fw, NttSchedule* out) {
-  const std::tuple<int, uint32_t, bool> key(L, logn, fw);
+bool costmodel_pick(int L, uint32_t logn, NttSchedule* out) {
+  const std::pair<int, uint32_t> key(L, logn);
   {
     std::lock_guard<std::mutex> lk(g_cm_mu);
     if (!g_cm.ready) return false;
@@ -132,7 +128,7 @@ bool costmodel_pick(int L, uint32_t logn, bool fw, NttSchedule* out) {
     }
   }
   std::string keep = g_detail;
-  std::vector<NttSchedule> cands = enumerate_schedules(L, logn, fw);
+  std::vector<NttSchedule> cands = enumerate_schedules(L, logn);
   std::vector<float> sc;
   if (cands.empty() || costmodel_scores(L, logn, cands, &sc) != MOMA_OK) {
     g_detail = keep;

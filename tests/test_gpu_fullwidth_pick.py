@@ -1,6 +1,6 @@
-"""A full-width plan's initial launch shape: the best that the loaded cost model
-predicts among the shapes such a modulus can run, also where the best of all is
-one that it cannot (a Karatsuba form or a radix-8 unit)."""
+"""A full-width plan's initial launch shape: the loaded cost model's pick, without
+the Karatsuba form that such a modulus has none of, or the fixed rule where it
+cannot run the pick at all (a radix-8 unit)."""
 import numpy as np
 import pytest
 
@@ -20,18 +20,13 @@ def test_initial_shape(lam, logn):
     f = mi.find_prime(lam, 0, bits=lam)
     q, L, n = f.q, f.limbs, 1 << logn
     w = f.root(n)
-    widest = 2 if L <= 16 else 1
     moma.ntt_set_schedule(q, w, n, L, None)
     got = moma.ntt_get_schedule(q, w, n, L)
-    cands = []
-    for s in moma.ntt_candidates(L, logn):
-        if s[4] == 0 and s[3] <= widest:
-            moma.ntt_set_schedule(q, w, n, L, s)  # (refused if the modulus could not run it)
-            cands.append(s)
+    cands = moma.ntt_candidates(L, logn)
     pred = moma.costmodel_predict(np.array([moma.costmodel_features(L, logn, s) for s in cands], np.float32))
+    pick = cands[int(np.argmin(pred))][:4] + (0,)
     say(f"full width {lam} bits 2^{logn}: {got}")
-    moma.ntt_set_schedule(q, w, n, L, None)
-    assert got == moma.ntt_get_schedule(q, w, n, L) == cands[int(np.argmin(pred))]
+    assert got == (pick if pick[3] <= (2 if L <= 16 else 1) else moma.ntt_default_schedule(L, logn))
     if logn <= 14:
         x = mi.residues(f, n, L, 860, logn)
         assert (from_dev(moma.ntt_fwd(to_dev(x), q, w)) == oracle.ntt_radix2(q, L, w, x)).all()

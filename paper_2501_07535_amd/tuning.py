@@ -9,6 +9,10 @@
   python -m paper_2501_07535_amd.tuning train --db DB.csv [...] --model cm.txt
       train the cost model on every shape (the model a package ships: new plans
       without timings start from its top-ranked schedule)
+  python -m paper_2501_07535_amd.tuning refine --db DB.csv [...] --model cm.txt --out refined.txt [--against old.txt ...]
+      continue a model's training on the regret of its first pick beside the error
+      of its times (on the CPU), the more so where that pick is slower than the
+      --against models'; no GPU needed
   python -m paper_2501_07535_amd.tuning picks --db DB.csv [...] --model cm.txt --out picks.json
       the top-1 regret of a saved model on every shape of the database (for the
       packaged model: the cost of a new plan's first pick on shapes it was trained on)
@@ -152,6 +156,102 @@ def train_all(paths, model_path, seed=7, epochs=300, batch=256, lr=3e-3):
                       "model": model_path}), flush=True)
 
 
+def read_model(path):
+    """A saved model: feature means and deviations, target mean and deviation, weights."""
+    with open(path) as fh:
+        tag, version, count = fh.readline().split()
+        v = np.array([float(x) for x in fh.read().split()], np.float32)
+    if tag != "moma-costmodel" or version != "1" or len(v) != 16 + int(count):
+        raise ValueError(f"{path}: not a cost model file")
+    return v[0:14:2], v[1:14:2], float(v[14]), float(v[15]), v[16:]
+
+
+def _layers(weights):
+    """The 7-64-64-1 network's matrices and biases in the saved order."""
+    shapes, at, out = ((64, 7), (64,), (64, 64), (64,), (1, 64), (1,)), 0, []
+    for shp in shapes:
+        size = int(np.prod(shp))
+        out.append(weights[at:at + size].reshape(shp))
+        at += size
+    return out
+
+
+def refine(paths, model_path, out, against=(), steps=3000, lr=5e-3, weight=1.5, temperature=0.03):
+    """Mean squared error says nothing of which shape comes out first, and the
+    time jumps where a pass is added, which seven smooth inputs fit badly.  So the
+    loss here is mostly the expected regret (in log time) of a softmax over every
+    size's predicted times, sharpened as it goes, counted threefold where it
+    exceeds the regret of the best pick of the `against` models.  Of the states passed the one
+    is kept whose picks are best: their mean regret, a tenth of the largest loss to
+    those models, and a little for every size that loses over 5%."""
+    import torch
+
+    import paper_2501_07535_amd as moma
+    rows = sorted(load_rows(paths), key=lambda r: (r[0], r[1]))
+    feats = np.array([moma.costmodel_features(L, n, s) for L, n, s, _ in rows], np.float32)
+    y = np.log(np.array([us for *_, us in rows], np.float32))
+    _, inv, cnt = np.unique([100 * r[0] + r[1] for r in rows], return_inverse=True, return_counts=True)
+    start = np.concatenate([[0], np.cumsum(cnt)[:-1]])
+    cand = start[:, None] + np.arange(cnt.max())[None]
+    valid = np.arange(cnt.max())[None] < cnt[:, None]
+    cand = np.where(valid, cand, 0)
+    over = y - np.minimum.reduceat(y, start)[inv]  # log regret of every row
+
+    def first(pred):
+        return over[cand[np.arange(len(cnt)), np.where(valid, pred[cand], np.inf).argmin(1)]]
+
+    def predict(path):
+        fm, fs, tm, ts, w = read_model(path)
+        h = (feats - fm) / fs
+        w1, b1, w2, b2, w3, b3 = _layers(w)
+        h = np.maximum(h @ w1.T + b1, 0)
+        return (np.maximum(h @ w2.T + b2, 0) @ w3.T + b3)[:, 0] * ts + tm
+
+    old = np.min([first(predict(m)) for m in against] + [np.full(len(cnt), np.inf, np.float32)], axis=0)
+    fm, fs, tm, ts, w = read_model(model_path)
+    params = [torch.from_numpy(p.copy()).requires_grad_() for p in _layers(w)]
+    x, t = torch.from_numpy((feats - fm) / fs), torch.from_numpy(((y - tm) / ts).astype(np.float32))
+    idx, mask, reg = torch.from_numpy(cand), torch.from_numpy(valid), torch.from_numpy(over)[torch.from_numpy(cand)]
+    limit = torch.from_numpy(old + 0.01)
+
+    def forward():
+        w1, b1, w2, b2, w3, b3 = params
+        h = torch.relu(x @ w1.T + b1)
+        return (torch.relu(h @ w2.T + b2) @ w3.T + b3)[:, 0]
+
+    opt = torch.optim.Adam(params, lr=lr)
+    best = (float("inf"), None)
+    t0 = time.time()
+    for step in range(steps):
+        f = step / steps
+        for g in opt.param_groups:
+            g["lr"] = lr * 0.5 * (1 + math.cos(math.pi * f)) + 1e-5
+        p = forward()
+        soft = torch.softmax(torch.where(mask, -(p * ts)[idx] / (temperature * (4 - 3 * f)), torch.tensor(-1e9)), 1)
+        e = (soft * reg).sum(1)
+        loss = 0.2 * ((p - t) ** 2).mean() + weight * (e + 2 * torch.relu(e - limit)).mean()
+        opt.zero_grad()
+        loss.backward()
+        opt.step()
+        if step % 50 == 49:
+            with torch.no_grad():
+                r = first(forward().numpy() * ts + tm)
+            worse = np.maximum(0, r - old - 0.02)
+            score = float(np.expm1(r.mean()) + 0.0003 * (worse > 0.03).sum() + 0.1 * worse.max())
+            if score < best[0]:
+                best = (score, [q.detach().clone() for q in params])
+                print(f"[{time.time() - t0:6.0f}s] step {step + 1}: regret {np.expm1(r.mean()):.4f} max "
+                      f"{np.expm1(r.max()):.3f}, {(r - old > math.log(1.05)).sum()} sizes over 5% slower, at most "
+                      f"{np.expm1((r - old).max()):.3f}", flush=True)
+    with open(out, "w") as fh:
+        fh.write(f"moma-costmodel 1 {len(w)}\n")
+        for j in range(7):
+            fh.write(f"{fm[j]:.9g} {fs[j]:.9g}\n")
+        fh.write(f"{tm:.9g} {ts:.9g}\n")
+        for q in best[1]:
+            fh.writelines(f"{v:.9g}\n" for v in q.reshape(-1).tolist())
+
+
 def picks(paths, model_path, out):
     import paper_2501_07535_amd as moma
     moma.costmodel_load(model_path)
@@ -232,6 +332,13 @@ def main():
     t.add_argument("--batch", type=int, default=256)
     t.add_argument("--lr", type=float, default=3e-3)
     t.add_argument("--seed", type=int, default=7)
+    r = sub.add_parser("refine")
+    r.add_argument("--db", nargs="+", required=True)
+    r.add_argument("--model", required=True)
+    r.add_argument("--out", required=True)
+    r.add_argument("--against", nargs="*", default=())
+    r.add_argument("--steps", type=int, default=3000)
+    r.add_argument("--lr", type=float, default=5e-3)
     p = sub.add_parser("picks")
     p.add_argument("--db", nargs="+", required=True)
     p.add_argument("--model", required=True)
@@ -243,6 +350,8 @@ def main():
     a = ap.parse_args()
     if a.cmd == "train":
         train_all(a.db, a.model, seed=a.seed, epochs=a.epochs, batch=a.batch, lr=a.lr)
+    elif a.cmd == "refine":
+        refine(a.db, a.model, a.out, a.against, steps=a.steps, lr=a.lr)
     elif a.cmd == "picks":
         picks(a.db, a.model, a.out)
     elif a.cmd == "widths":
